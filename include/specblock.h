@@ -83,7 +83,8 @@ typedef struct sb_config {
   int32_t page_size;        /* K/V page size in tokens; must be 16            */
   int32_t max_pages;        /* page-table row length (pages per sequence),
                                1..16384                                       */
-  int32_t prefill_chunk;    /* rows per prefill step (multiple of 16)         */
+  int32_t prefill_chunk;    /* 16..512, a multiple of 16; no longer read: a
+                               prefill runs in passes of up to 2048 rows      */
   int32_t draft_vocab;      /* drafter output vocabulary: 0 = the target's;
                                else a multiple of 16 in 10..vocab, the
                                drafter's reduced vocabulary (App. A: the most

@@ -54,7 +54,11 @@ __device__ __forceinline__ uint4 keep_slots(uint4 v, int first, int nvalid) {
 // read once for up to 16 NQ QT query vectors.  With several splits each
 // workgroup writes (O, m, l) partials that attn_merge combines; with one
 // split the kernel writes the output.
-template <typename T, int HD, int NQ, int QT>
+//
+// CAUSAL (prefill pieces, see CallPlan::kv_row): s is a piece, all of its
+// keys are in the paged cache (no segment), and a row attends to the entries
+// up to its own, kv_dst.
+template <typename T, int HD, int NQ, int QT, bool CAUSAL>
 __global__ __launch_bounds__(NQ * 64) void tree_attn_kernel(
     const T* __restrict__ q, CallPlan p, KVView kv, int H, int Hkv,
     int split_tokens, float scale, float* __restrict__ o_part,
@@ -122,12 +126,17 @@ __global__ __launch_bounds__(NQ * 64) void tree_attn_kernel(
   bool wave_live = false;
 #pragma unroll
   for (int j = 0; j < QT; ++j) wave_live |= live[j];
+  int n_vis[QT];              // causal: entries the row attends to
+  if constexpr (CAUSAL) {
+#pragma unroll
+    for (int j = 0; j < QT; ++j) n_vis[j] = p.kv_dst[qrow[j]] + 1;
+  }
 
   const T* kpool = static_cast<const T*>(kv.k);
   const T* vpool = static_cast<const T*>(kv.v);
   const T* skp = static_cast<const T*>(kv.seg_k);
   const T* svp = static_cast<const T*>(kv.seg_v);
-  const int* ptab = kv.page_table + (size_t)s * kv.max_pages;
+  const int* ptab = kv.page_table + (size_t)(CAUSAL ? p.kv_row[s] : s) * kv.max_pages;
   // committed keys: the prefix, within the page table and the length bound
   // (a bound below a prefix skips the entries past it)
   const int Tp = min(min(p.prefix_len[s], kv.max_pages * 16), key_cap);
@@ -141,7 +150,8 @@ __global__ __launch_bounds__(NQ * 64) void tree_attn_kernel(
   const int t0 = bz * sp_tok;
   const int t1 = min(Tp, t0 + sp_tok);
   const bool last_split = bz == gridDim.z - 1;
-  const int L = last_split ? min(p.seg_len[s], kv.seg_pages * 16) : 0;
+  const int L =
+      !CAUSAL && last_split ? min(p.seg_len[s], kv.seg_pages * 16) : 0;
   const int n_pre = t1 > t0 ? (t1 - t0 + 31) / 32 : 0;
   const int n_tiles = n_pre + (L + 31) / 32;
   // the split's page-table entries, read once so that no tile fetch waits
@@ -194,9 +204,11 @@ __global__ __launch_bounds__(NQ * 64) void tree_attn_kernel(
       const T* va = vp + (h ? b1 : b0) + hd * 16 + vpart * (16 / ES);
       dst[e] = *reinterpret_cast<const uint4*>(c < KCH ? ka : va);
     }
-    const int wc = min(max(i - n_pre, 0), p.vis_words - 1);
+    if constexpr (!CAUSAL) {
+      const int wc = min(max(i - n_pre, 0), p.vis_words - 1);
 #pragma unroll
-    for (int j = 0; j < QT; ++j) vdst[j] = p.vis[(size_t)qrow[j] * p.vis_words + wc];
+      for (int j = 0; j < QT; ++j) vdst[j] = p.vis[(size_t)qrow[j] * p.vis_words + wc];
+    }
   };
   // valid keys of tile i
   auto n_valid = [&](int i) -> int {
@@ -243,8 +255,12 @@ __global__ __launch_bounds__(NQ * 64) void tree_attn_kernel(
     Frag8<T> pf[QT];
 #pragma unroll
     for (int j = 0; j < QT; ++j) {
-      const uint32_t bits =
+      uint32_t bits =
           seg ? ((vis_ok && qvalid[j]) ? (valid & vword[j]) : 0u) : valid;
+      if constexpr (CAUSAL) {
+        const int left = n_vis[j] - (t0 + i * 32);
+        bits = left >= 32 ? valid : left > 0 ? valid & ((1u << left) - 1u) : 0u;
+      }
       float sc[8];
       float mx = SB_NEG;
 #pragma unroll
@@ -311,7 +327,7 @@ __global__ __launch_bounds__(NQ * 64) void tree_attn_kernel(
         const int i = i0 + d;
         uint32_t vword[QT];
 #pragma unroll
-        for (int j = 0; j < QT; ++j) vword[j] = visr[d][j];
+        for (int j = 0; j < QT; ++j) vword[j] = CAUSAL ? 0u : visr[d][j];
         fetch(min(i + DEPTH, n_tiles - 1), stg[d], visr[d]);
         if (i < n_tiles) compute(i, i & 1, vword);
         if (i + 1 < n_tiles) stash(i + 1, (i + 1) & 1, stg[(d + 1) % DEPTH]);
@@ -442,7 +458,8 @@ __device__ __forceinline__ attn_f32x16_t mma32_attn(attn_u32x4_t a, attn_u32x4_t
 // with fixed splits of split_tokens keys; else a grid of kAttnSlots
 // balanced items (above), and the split count of every row's sequence is
 // written to split_rows for the merge.
-template <int HD, int NW>
+// CAUSAL: prefill pieces, as in tree_attn_kernel (fixed splits only).
+template <int HD, int NW, bool CAUSAL>
 __global__ __launch_bounds__(NW * 64) void tree_attn32_kernel(
     const bf16_t* __restrict__ q, CallPlan p, KVView kv, int H, int Hkv,
     int split_tokens, float scale, float* __restrict__ o_part,
@@ -515,6 +532,12 @@ __global__ __launch_bounds__(NW * 64) void tree_attn32_kernel(
         q + ((size_t)qrow * H + qh) * HD + 16 * j + 8 * h);
     if (!qvalid) qf[j] = attn_u32x4_t{0u, 0u, 0u, 0u};
   }
+  // causal: entries this lane's row, and the piece's first row, attend to
+  int n_vis = 0, vis_first = 0;
+  if constexpr (CAUSAL) {
+    n_vis = p.kv_dst[qrow] + 1;
+    vis_first = p.kv_dst[row0] + 1;
+  }
   float m_run = SB_NEG, l_run = 0.f;
   attn_f32x16_t acc[HB];
 #pragma unroll
@@ -526,7 +549,7 @@ __global__ __launch_bounds__(NW * 64) void tree_attn32_kernel(
   const bf16_t* vpool = static_cast<const bf16_t*>(kv.v);
   const bf16_t* skp = static_cast<const bf16_t*>(kv.seg_k);
   const bf16_t* svp = static_cast<const bf16_t*>(kv.seg_v);
-  const int* ptab = kv.page_table + (size_t)s * kv.max_pages;
+  const int* ptab = kv.page_table + (size_t)(CAUSAL ? p.kv_row[s] : s) * kv.max_pages;
   // committed keys: the prefix, within the page table and the length bound
   // (a bound below a prefix skips the entries past it)
   const int Tp = min(min(p.prefix_len[s], kv.max_pages * 16), key_cap);
@@ -537,7 +560,8 @@ __global__ __launch_bounds__(NW * 64) void tree_attn32_kernel(
   const int t0 = zs * split_tok;
   const int t1 = min(Tp, t0 + split_tok);
   const bool last_split = zs == nzs - 1;
-  const int L = last_split ? min(p.seg_len[s], kv.seg_pages * 16) : 0;
+  const int L =
+      !CAUSAL && last_split ? min(p.seg_len[s], kv.seg_pages * 16) : 0;
   const int n_pre = t1 > t0 ? (t1 - t0 + KT - 1) / KT : 0;
   const int n_tiles = n_pre + (L + KT - 1) / KT;
   const int pg0 = t0 >> 4;
@@ -598,10 +622,12 @@ __global__ __launch_bounds__(NW * 64) void tree_attn32_kernel(
       const bf16_t* src = (e * NT < KCH ? kp : vp) + base + c_off[e];
       dst[e] = *reinterpret_cast<const attn_u32x4_t*>(src);
     }
-    const int w0 = min(max(2 * (i - n_pre), 0), p.vis_words - 1);
-    const int w1 = min(w0 + 1, p.vis_words - 1);
-    vdst[0] = p.vis[(size_t)qrow * p.vis_words + w0];
-    vdst[1] = p.vis[(size_t)qrow * p.vis_words + w1];
+    if constexpr (!CAUSAL) {
+      const int w0 = min(max(2 * (i - n_pre), 0), p.vis_words - 1);
+      const int w1 = min(w0 + 1, p.vis_words - 1);
+      vdst[0] = p.vis[(size_t)qrow * p.vis_words + w0];
+      vdst[1] = p.vis[(size_t)qrow * p.vis_words + w1];
+    }
   };
   auto n_valid = [&](int i) -> int {
     return i < n_pre ? min(KT, t1 - (t0 + i * KT)) : min(KT, L - (i - n_pre) * KT);
@@ -635,7 +661,8 @@ __global__ __launch_bounds__(NW * 64) void tree_attn32_kernel(
     if (!wave_live) return;
     const bool seg = i >= n_pre;
     const int nv = n_valid(i);
-    const bool full = !seg && nv == KT;
+    const bool full =
+        !seg && nv == KT && (!CAUSAL || t0 + (i + 1) * KT <= vis_first);
     const int w = i - n_pre;
     attn_f32x16_t sc[2];
 #pragma unroll
@@ -686,6 +713,10 @@ __global__ __launch_bounds__(NW * 64) void tree_attn32_kernel(
         const int nb = min(max(nv - 32 * b, 0), 32);
         uint32_t m = nb >= 32 ? 0xFFFFFFFFu : ((1u << nb) - 1u);
         if (seg) m &= (qvalid && 2 * w + b < p.vis_words) ? vw[b] : 0u;
+        if constexpr (CAUSAL) {
+          const int left = n_vis - (t0 + i * KT + 32 * b);
+          m = left >= 32 ? m : left > 0 ? m & ((1u << left) - 1u) : 0u;
+        }
         m >>= 4 * h;
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
@@ -744,7 +775,7 @@ __global__ __launch_bounds__(NW * 64) void tree_attn32_kernel(
 #pragma unroll
       for (int d = 0; d < DEPTH; ++d) {
         const int i = i0 + d;
-        uint32_t vw[2] = {visr[d][0], visr[d][1]};
+        uint32_t vw[2] = {CAUSAL ? 0u : visr[d][0], CAUSAL ? 0u : visr[d][1]};
         fetch(min(i + DEPTH, n_tiles - 1), stg[d], visr[d]);
         if (i < n_tiles) compute(i, i & 1, vw);
         if (i + 1 < n_tiles) stash(i + 1, (i + 1) & 1, stg[(d + 1) % DEPTH]);
@@ -989,10 +1020,11 @@ void launch_tree_attn(const T* q, const CallPlan& p, const KVView& kv,
       const hipEvent_t kb32 = merge ? nullptr : eb;
 #define SB_ATTN32(HD_, NW_)                                                    \
   if (hd == HD_ && a.nq == NW_) {                                             \
-    hipExtLaunchKernelGGL(tree_attn32_kernel<HD_, NW_>, g32, dim3(NW_ * 64),  \
-                          0, st, ka, kb32, 0, q, p, kv, H, Hkv, split_tokens, \
-                          scale, o_part, ml, out, a.groups, ms, sr,           \
-                          max_prefix);                                        \
+    auto k = p.kv_row != nullptr ? tree_attn32_kernel<HD_, NW_, true>         \
+                                 : tree_attn32_kernel<HD_, NW_, false>;       \
+    hipExtLaunchKernelGGL(k, g32, dim3(NW_ * 64), 0, st, ka, kb32, 0, q, p,   \
+                          kv, H, Hkv, split_tokens, scale, o_part, ml, out,   \
+                          a.groups, ms, sr, max_prefix);                      \
     if (merge)                                                                \
       launch_attn_merge<T>(p, H, hd, ms, o_part, ml, out, st, eb, sr);        \
     return;                                                                   \
@@ -1004,7 +1036,9 @@ void launch_tree_attn(const T* q, const CallPlan& p, const KVView& kv,
   {
 #define SB_ATTN(HD_, NQ_, QT_)                                                 \
   if (hd == HD_ && a.nq == NQ_ && a.qt == QT_) {                              \
-    hipExtLaunchKernelGGL(tree_attn_kernel<T, HD_, NQ_, QT_>, grid,           \
+    auto k = p.kv_row != nullptr ? tree_attn_kernel<T, HD_, NQ_, QT_, true>   \
+                                 : tree_attn_kernel<T, HD_, NQ_, QT_, false>; \
+    hipExtLaunchKernelGGL(k, grid,                                            \
                           dim3(NQ_ * 64), 0, st, ka, kb, 0, q, p, kv, H, Hkv, \
                           split_tokens, scale, o_part, ml, out, max_prefix);  \
     if (n_split > 1)                                                          \

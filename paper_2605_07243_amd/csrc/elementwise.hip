@@ -2,6 +2,7 @@
 // residual add of split-K partials, RoPE + K/V segment write, SwiGLU, the
 // layer-wise shift operand and the drafter input fusion operand.
 // One workgroup per call row; the active row count is read on the device.
+#include "bounds.h"
 #include "common.h"
 #include "kernels.h"
 
@@ -303,14 +304,15 @@ void launch_residual(float* x, const float* P, int ks, size_t part_stride,
 
 // RoPE (rotate-half pairs (j, j + hd/2), angle pos * theta^(-2j/hd)) on the
 // Q and K heads of the summed QKV projection; Q -> q [cap][H][hd], K and V ->
-// the row's slot of its sequence's segment pages.  Grid (rows, item blocks):
+// the row's slot of its sequence's segment pages, or, for a prefill pass,
+// straight into the row's cache entry (no copy from a segment afterwards, and
+// the later pieces of the pass find them there).  Grid (rows, item blocks):
 // an item is four rotation pairs of one Q/K head, or four V columns; one
 // item per thread, its partials summed in one pass.
 template <typename T, bool EARLY>
 __global__ __launch_bounds__(256) void qkv_post_kernel(
     const float* __restrict__ P, int ks, size_t part_stride, CallPlan p, int H,
-    int Hkv, int hd, float theta, T* __restrict__ q, T* __restrict__ seg_k,
-    T* __restrict__ seg_v, int seg_pages) {
+    int Hkv, int hd, float theta, T* __restrict__ q, KVView kv) {
   __shared__ __attribute__((aligned(16))) float cs[128];
   __shared__ __attribute__((aligned(16))) float sn[128];
   const int i = blockIdx.x;
@@ -351,9 +353,17 @@ __global__ __launch_bounds__(256) void qkv_post_kernel(
       return;
     }
   }
-  const int seq = p.seq[i], slot = p.slot[i];
-  const int page = slot >> 4, sl = slot & 15;
-  const size_t page_base = (size_t)seq * seg_pages + page;
+  // the page (of the segment pool, or of the cache) and slot of the row's K/V
+  const bool paged = p.kv_row != nullptr;
+  const int seq = p.seq[i], slot = paged ? p.kv_dst[i] : p.slot[i];
+  const int sl = slot & 15;
+  const size_t page_base =
+      paged ? (size_t)checked_index(
+                  kv.page_table[(size_t)seq * kv.max_pages + (slot >> 4)],
+                  kv.n_pages, kv.err, kDevPage)
+            : (size_t)seq * kv.seg_pages + (slot >> 4);
+  T* kd = static_cast<T*>(paged ? kv.k : kv.seg_k);
+  T* vd = static_cast<T*>(paged ? kv.v : kv.seg_v);
   const double pos = (double)p.pos[i];
   for (int t = threadIdx.x; t < half; t += blockDim.x) {
     // angle in double, reduced to [-pi, pi] before the fp32 sincos
@@ -375,11 +385,11 @@ __global__ __launch_bounds__(256) void qkv_post_kernel(
     const float4 rb = make_float4(b.x * c4.x + a.x * s4.x, b.y * c4.y + a.y * s4.y,
                                   b.z * c4.z + a.z * s4.z, b.w * c4.w + a.w * s4.w);
     T* dst = head < H ? q + ((size_t)i * H + head) * hd
-                      : seg_k + ((page_base * Hkv + (head - H)) * 16 + sl) * hd;
+                      : kd + ((page_base * Hkv + (head - H)) * 16 + sl) * hd;
     store4<T>(dst + j, ra);
     store4<T>(dst + j + half, rb);
   } else if (idx < n_items) {
-    T* dv = seg_v + ((page_base * Hkv + head) * hd + j) * 16 + sl;
+    T* dv = vd + ((page_base * Hkv + head) * hd + j) * 16 + sl;
     dv[0] = Elem<T>::from_f32(a.x);
     dv[16] = Elem<T>::from_f32(a.y);
     dv[32] = Elem<T>::from_f32(a.z);
@@ -390,15 +400,13 @@ __global__ __launch_bounds__(256) void qkv_post_kernel(
 template <typename T>
 void launch_qkv_post(const float* P, int ks, size_t part_stride,
                      const CallPlan& p, int H, int Hkv, int hd, float theta,
-                     T* q, void* seg_k, void* seg_v, int seg_pages,
-                     hipStream_t st) {
+                     T* q, const KVView& kv, hipStream_t st) {
   const int items = (H + Hkv) * (hd / 8) + Hkv * (hd / 4);
   auto k = p.cap <= kEarlyRows && !g_rows_likely_empty
                ? qkv_post_kernel<T, true>
                : qkv_post_kernel<T, false>;
   k<<<dim3(p.cap, (items + 255) / 256), 256, 0, st>>>(
-      P, ks, part_stride, p, H, Hkv, hd, theta, q, (T*)seg_k, (T*)seg_v,
-      seg_pages);
+      P, ks, part_stride, p, H, Hkv, hd, theta, q, kv);
 }
 
 // out = silu(gate) * up, four columns per thread; grid (rows, F / 1024).
@@ -598,8 +606,8 @@ void launch_rows_to_elem(const float* src, const int* idx, const int* n,
   template void launch_norm_rows<T>(const T*, int, int, const float*, float,   \
                                     T*, hipStream_t);                          \
   template void launch_qkv_post<T>(const float*, int, size_t, const CallPlan&, \
-                                   int, int, int, float, T*, void*, void*,     \
-                                   int, hipStream_t);                          \
+                                   int, int, int, float, T*, const KVView&,    \
+                                   hipStream_t);                               \
   template void launch_swiglu<T>(const float*, int, size_t, const int*, int,   \
                                  int, T*, hipStream_t);                        \
   template void launch_shift_prep<T>(const float*, const CallPlan&, int, T*,   \

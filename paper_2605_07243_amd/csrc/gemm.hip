@@ -647,11 +647,6 @@ void gemm_time_next_launch(hipEvent_t start, hipEvent_t stop) {
 
 bool gemm_time_pending() { return g_ev_start != nullptr; }
 
-int gemm_ksplit(int N, int K, int elem_bytes) {
-  // fewest row tiles -> most K-chunks
-  return gemm_plan(N, K, 1, elem_bytes).ks;
-}
-
 namespace {
 
 template <bool SWIGLU, int VR = 0>

@@ -29,6 +29,12 @@ struct CallPlan {
   int* seg_len;      // [max_seqs] valid segment slots of the sequence
   int* out_row;      // [cap] destination index of per-row outputs (or -1)
   int* kv_dst;       // [cap] cache entry the row's K/V is committed to (-1)
+  // Causal prefill plans only (else null): [n_seqs] sequence (page-table
+  // row) of each piece.  A piece is a run of at most kPieceRows consecutive
+  // prompt rows; seq_off and prefix_len are then indexed by piece,
+  // prefix_len counts the piece's own keys too, K/V go straight to cache
+  // entry kv_dst, and a row attends to the entries up to its own.
+  int* kv_row = nullptr;
   int cap;
   int vis_words;
   int n_seqs;        // host value: sequences with valid seq_off entries
@@ -37,13 +43,13 @@ struct CallPlan {
 // K/V addressing: paged prefix + per-sequence segment, both in the
 // [kvh][16][hd] (K) / [kvh][hd][16] (V) page layout, one layer at a time.
 struct KVView {
-  const void* k;            // layer base of the page pool
-  const void* v;
+  void* k;                  // layer base of the page pool
+  void* v;
   const int* page_table;    // [S][max_pages]
   int max_pages;
   int n_pages;              // pages in the pool (indices are clamped to it)
-  const void* seg_k;        // layer base of the segment pool [S][seg_pages]
-  const void* seg_v;
+  void* seg_k;              // layer base of the segment pool [S][seg_pages]
+  void* seg_v;
   int seg_pages;            // pages per sequence in the segment pool
   int* err = nullptr;       // debug status word (out-of-range pages), or null
 };
@@ -61,14 +67,12 @@ bool gemm_shape_ok(int N, int K, int elem_bytes);
 // projections); the many-row planner may then pick other tile shapes.
 GemmPlan gemm_plan(int N, int K, int m_cap, int elem_bytes,
                    bool retile = false);
-// Largest K-split any call of this shape may use (partial-buffer sizing).
 // Kernel-attached timing of the next projection-GEMM launch (profiling).
 void gemm_time_next_launch(hipEvent_t start, hipEvent_t stop);
 bool gemm_time_pending();
 // Kernel-attached timing of the next tree-attention call (kernel + merge).
 void attn_time_next_launch(hipEvent_t start, hipEvent_t stop);
 bool attn_time_pending();
-int gemm_ksplit(int N, int K, int elem_bytes);
 // P[ks][m][n] = X[m] . W[n] over K-chunk ks for the first *m_count rows.
 // bf16 W is fragment-packed, f32 W row-major.  ksplit <= 0: the plan's
 // split; otherwise at most ksplit K-chunks.  Returns the K-chunks written.
@@ -119,11 +123,12 @@ void launch_residual(float* x, const float* P, int ks, size_t part_stride,
 template <typename T>
 void launch_norm_rows(const T* src, int n_rows, int d, const float* g,
                       float eps, T* out, hipStream_t st);
+// K/V rows go to the segment pool of kv (slot p.slot of sequence p.seq), or,
+// for a causal plan (p.kv_row), to entry p.kv_dst of the paged cache.
 template <typename T>
 void launch_qkv_post(const float* P, int ks, size_t part_stride,
                      const CallPlan& p, int H, int Hkv, int hd, float theta,
-                     T* q, void* seg_k, void* seg_v, int seg_pages,
-                     hipStream_t st);
+                     T* q, const KVView& kv, hipStream_t st);
 template <typename T>
 void launch_swiglu(const float* P, int ks, size_t part_stride, const int* n,
                    int cap, int F, T* out, hipStream_t st);
@@ -301,17 +306,39 @@ void launch_seg_to_cache(const CallPlan& p, const KVPools& kv, int S,
 void launch_commit_state(const TreeDims& td, const sb_seqs& sq,
                          const sb_accept_out& acc, const CommitInfo& ci,
                          const float* taps, hipStream_t st);
-// Prompt tokens outside 0 .. V - 1 are clamped into it (and recorded in the
-// debug status word err when it is not null).
-void launch_plan_prefill_target(int S, int s, int a, int n, const int* prompt,
-                                int ld, const CallPlan& p, int V, int* err,
-                                hipStream_t st);
-void launch_plan_prefill_draft(int S, int s, int a, int n, const int* prompt,
-                               int ld, const CallPlan& p, int* n_aux, int V,
-                               int* err, hipStream_t st);
-void launch_prefill_finish(const sb_seqs& sq, int s, int len, int d,
-                           const float* taps_pf, int n_last,
-                           const int* root_arg, hipStream_t st);
+// Prefill passes (see prefill_impl): up to kPrefillRows prompt rows of any
+// sequences in one forward, cut into pieces of at most kPieceRows rows for
+// the attention.  Passed to the kernels by value.
+constexpr int kPieceRows = 64;
+constexpr int kPrefillRows = 2048;
+constexpr int kMaxPieces = kPrefillRows / kPieceRows + SB_MAX_SEQS;
+struct PrefillPass {
+  int n_pieces, n_rows;
+  int a[kMaxPieces];             // first prompt position of the piece
+  int row0[kMaxPieces + 1];      // its first call row
+  unsigned char seq[kMaxPieces];
+};
+// Sequences whose prompt ends in a pass: call row of the last position;
+// first: how many prompts ended in earlier passes.
+struct PrefillEnds {
+  int n, first;
+  int len[SB_MAX_SEQS];
+  short row[SB_MAX_SEQS];
+  unsigned char seq[SB_MAX_SEQS];
+};
+// Call plan of a pass: the prompt rows of the target, or the drafter's
+// catch-up rows.  Prompt tokens outside 0 .. V - 1 are clamped into it (and
+// recorded in the debug status word err when it is not null).
+void launch_plan_prefill(const PrefillPass& pass, bool drafter,
+                         const int* prompt, int ld, const CallPlan& p,
+                         int* n_aux, int V, int* err, hipStream_t st);
+// T and cond_taps (taps row 1 + row) of the sequences that end, their
+// LM-head operand rows src[row] in out[first ..] and sequences in
+// out_seq[first ..]; *n = rows of `out` so far.
+template <typename T>
+void launch_prefill_ends(const PrefillEnds& ends, const sb_seqs& sq, int d,
+                         const float* taps_pf, const T* src, T* out, int* n,
+                         int* out_seq, hipStream_t st);
 void launch_copy_f32(float* dst, const float* src, int n, hipStream_t st);
 void launch_set_int(int* p, int v, hipStream_t st);
 // *dst = *src (one thread; e.g. a row count captured for the profiler)

@@ -510,83 +510,66 @@ __global__ void commit_state_kernel(TreeDims td, sb_seqs sq, sb_accept_out acc,
   }
 }
 
-// Prefill of sequence s, chunk [a, a + n): target rows (causal chain).
-__global__ void plan_prefill_target_kernel(int S, int s, int a, int n,
-                                           const int* __restrict__ prompt,
-                                           int ld, CallPlan p, int V,
-                                           int* __restrict__ err) {
-  if (threadIdx.x == 0) {
-    for (int q = 0; q <= S; ++q) p.seq_off[q] = q <= s ? 0 : n;
-    for (int q = 0; q < S; ++q) {
-      p.prefix_len[q] = q == s ? a : 0;
-      p.seg_len[q] = q == s ? n : 0;
-    }
-    *p.n = n;
-  }
-  for (int j = threadIdx.x; j < n; j += blockDim.x) {
-    p.seq[j] = s;
-    p.slot[j] = j;
-    p.pos[j] = a + j;
-    p.token[j] = checked_index(prompt[(size_t)s * ld + a + j], V, err, kDevToken);
-    p.k[j] = 1;
-    p.pred[j] = j;
-    p.cond[j] = -1;
-    p.out_row[j] = 1 + j;          // taps slot in the prefill tap buffer
-    p.kv_dst[j] = a + j;
-    for (int w = 0; w < p.vis_words; ++w) {
-      uint32_t bits = 0u;
-      for (int q = 32 * w; q < 32 * w + 32 && q <= j; ++q) bits |= 1u << (q & 31);
-      p.vis[(size_t)j * p.vis_words + w] = bits;
+// Call plan of a prefill pass, one wave per piece: prompt position a + t of
+// the piece's sequence.  Target rows run token x_{a+t} at that position and
+// leave their taps in row 1 + i of the tap buffer (row 0: the position before
+// the pass).  Drafter catch-up rows are K = 1 blocks started at position
+// a + t with token x_{a+t}, at position a + t + 1, conditioned on the taps of
+// position a + t - 1, row i of the tap buffer (none for position 0).
+__global__ __launch_bounds__(kPieceRows) void plan_prefill_kernel(
+    PrefillPass pass, int drafter, const int* __restrict__ prompt, int ld,
+    CallPlan p, int* __restrict__ n_aux, int V, int* __restrict__ err) {
+  const int j = blockIdx.x, t = threadIdx.x;
+  const int i0 = pass.row0[j], n = pass.row0[j + 1] - i0;
+  const int a = pass.a[j], s = pass.seq[j];
+  if (t == 0) {
+    p.seq_off[j] = i0;
+    p.prefix_len[j] = a + n;
+    p.seg_len[j] = 0;
+    p.kv_row[j] = s;
+    if (j == 0) {
+      p.seq_off[pass.n_pieces] = pass.n_rows;
+      *p.n = pass.n_rows;
+      *n_aux = pass.n_rows;
     }
   }
+  if (t >= n) return;
+  const int i = i0 + t;
+  p.seq[i] = s;
+  p.slot[i] = 0;
+  p.pos[i] = a + t + drafter;
+  p.token[i] = checked_index(prompt[(size_t)s * ld + a + t], V, err, kDevToken);
+  p.k[i] = 1;
+  p.pred[i] = i;
+  p.cond[i] = drafter && a + t >= 1 ? i : -1;
+  p.out_row[i] = drafter ? -1 : 1 + i;
+  p.kv_dst[i] = a + t;
 }
 
-// Prefill drafter catch-up rows for positions a+1 .. a+n: row r is a K = 1
-// block started at position a + r with token x_{a+r}, conditioned on the
-// target taps of position a + r - 1 (tap buffer slot r; none for position 1).
-__global__ void plan_prefill_draft_kernel(int S, int s, int a, int n,
-                                          const int* __restrict__ prompt,
-                                          int ld, CallPlan p,
-                                          int* __restrict__ n_aux, int V,
-                                          int* __restrict__ err) {
+// Prompts that end in a pass, one workgroup each: T = len, cond_taps = the
+// taps of position len - 1, and the LM-head operand of that row (the next
+// row of `out`) with its sequence, for one LM head after the last pass.
+template <typename T>
+__global__ __launch_bounds__(1024) void prefill_ends_kernel(
+    PrefillEnds ends, sb_seqs sq, int d, const float* __restrict__ taps_pf,
+    const T* __restrict__ src, T* __restrict__ out, int* __restrict__ n,
+    int* __restrict__ out_seq) {
+  const int j = blockIdx.x, s = ends.seq[j];
+  constexpr int V = 16 / sizeof(T);       // d % 32 == 0
+  const uint4* __restrict__ a =
+      reinterpret_cast<const uint4*>(src + (size_t)ends.row[j] * d);
+  uint4* __restrict__ o =
+      reinterpret_cast<uint4*>(out + (size_t)(ends.first + j) * d);
+  for (int e = threadIdx.x; e < d / V; e += 1024) o[e] = a[e];
+  float4* __restrict__ ct =
+      reinterpret_cast<float4*>(sq.cond_taps + (size_t)s * 3 * d);
+  const float4* __restrict__ tp = reinterpret_cast<const float4*>(
+      taps_pf + (size_t)(1 + ends.row[j]) * 3 * d);
+  for (int e = threadIdx.x; e < 3 * d / 4; e += 1024) ct[e] = tp[e];
   if (threadIdx.x == 0) {
-    for (int q = 0; q <= S; ++q) p.seq_off[q] = q <= s ? 0 : n;
-    for (int q = 0; q < S; ++q) {
-      p.prefix_len[q] = q == s ? a : 0;
-      p.seg_len[q] = q == s ? n : 0;
-    }
-    *p.n = n;
-    *n_aux = n;
-  }
-  for (int r = threadIdx.x; r < n; r += blockDim.x) {
-    p.seq[r] = s;
-    p.slot[r] = r;
-    p.pos[r] = a + 1 + r;
-    p.token[r] = checked_index(prompt[(size_t)s * ld + a + r], V, err, kDevToken);
-    p.k[r] = 1;
-    p.pred[r] = r;
-    p.cond[r] = (a + r >= 1) ? r : -1;
-    p.out_row[r] = -1;
-    p.kv_dst[r] = a + r;
-    for (int w = 0; w < p.vis_words; ++w) {
-      uint32_t bits = 0u;
-      for (int q = 32 * w; q < 32 * w + 32 && q <= r; ++q) bits |= 1u << (q & 31);
-      p.vis[(size_t)r * p.vis_words + w] = bits;
-    }
-  }
-}
-
-// Prefill end of sequence s: T = len, root = argmax of the last row,
-// cond_taps = taps of position len - 1 (tap buffer slot n_last).
-__global__ void prefill_finish_kernel(sb_seqs sq, int s, int len, int d,
-                                      const float* __restrict__ taps_pf,
-                                      int n_last, const int* __restrict__ root_arg) {
-  float* dst = sq.cond_taps + (size_t)s * 3 * d;
-  const float* src = taps_pf + (size_t)n_last * 3 * d;
-  for (int e = threadIdx.x; e < 3 * d; e += blockDim.x) dst[e] = src[e];
-  if (threadIdx.x == 0) {
-    sq.T[s] = len;
-    sq.root[s] = root_arg[0];
+    sq.T[s] = ends.len[j];
+    out_seq[ends.first + j] = s;
+    if (j == 0) *n = ends.first + ends.n;
   }
 }
 
@@ -807,24 +790,25 @@ void launch_commit_state(const TreeDims& td, const sb_seqs& sq,
                          const float* taps, hipStream_t st) {
   commit_state_kernel<<<td.S, 1024, 0, st>>>(td, sq, acc, ci, taps);
 }
-void launch_plan_prefill_target(int S, int s, int a, int n, const int* prompt,
-                                int ld, const CallPlan& p, int V, int* err,
-                                hipStream_t st) {
-  plan_prefill_target_kernel<<<1, 256, 0, st>>>(S, s, a, n, prompt, ld, p, V,
-                                                err);
+void launch_plan_prefill(const PrefillPass& pass, bool drafter,
+                         const int* prompt, int ld, const CallPlan& p,
+                         int* n_aux, int V, int* err, hipStream_t st) {
+  plan_prefill_kernel<<<pass.n_pieces, kPieceRows, 0, st>>>(
+      pass, drafter ? 1 : 0, prompt, ld, p, n_aux, V, err);
 }
-void launch_plan_prefill_draft(int S, int s, int a, int n, const int* prompt,
-                               int ld, const CallPlan& p, int* n_aux, int V,
-                               int* err, hipStream_t st) {
-  plan_prefill_draft_kernel<<<1, 256, 0, st>>>(S, s, a, n, prompt, ld, p,
-                                               n_aux, V, err);
+template <typename T>
+void launch_prefill_ends(const PrefillEnds& ends, const sb_seqs& sq, int d,
+                         const float* taps_pf, const T* src, T* out, int* n,
+                         int* out_seq, hipStream_t st) {
+  prefill_ends_kernel<T><<<ends.n, 1024, 0, st>>>(ends, sq, d, taps_pf, src,
+                                                  out, n, out_seq);
 }
-void launch_prefill_finish(const sb_seqs& sq, int s, int len, int d,
-                           const float* taps_pf, int n_last,
-                           const int* root_arg, hipStream_t st) {
-  prefill_finish_kernel<<<1, 256, 0, st>>>(sq, s, len, d, taps_pf, n_last,
-                                           root_arg);
-}
+template void launch_prefill_ends<float>(const PrefillEnds&, const sb_seqs&,
+                                         int, const float*, const float*,
+                                         float*, int*, int*, hipStream_t);
+template void launch_prefill_ends<bf16_t>(const PrefillEnds&, const sb_seqs&,
+                                          int, const float*, const bf16_t*,
+                                          bf16_t*, int*, int*, hipStream_t);
 void launch_copy_f32(float* dst, const float* src, int n, hipStream_t st) {
   copy_f32_kernel<<<(n + 255) / 256 < 1024 ? (n + 255) / 256 : 1024, 256, 0,
                     st>>>(dst, src, n);
