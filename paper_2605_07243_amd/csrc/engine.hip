@@ -122,10 +122,12 @@ Dims derive(const sb_config& c) {
 
 struct AdaptBufs {
   void* A;        // [adapt_cap][d] elem: LM-head operands
+  void* At;       // [d][64] bf16: the same as MFMA operands of the update
   float* Z;       // [adapt_cap][Vd] training-head logits, then gradients
   float* Z0;      // [adapt_cap][Vd] pre-deployment-head logits
   float* part;    // vocabulary chunk records of Z (top-10)
   float* part0;   // vocabulary chunk records of Z0 (top-1)
+  float* stat;    // [adapt_cap][kAdaptStat]
   float* psi;     // [adapt_cap][15]
   float* ds;      // [adapt_cap][4] rank-head score gradients
   float* loss;    // [adapt_cap]
@@ -240,10 +242,12 @@ static size_t layout(const Dims& D, void* base, sb_ctx* c) {
   // stream while inference uses the ones above)
   const size_t ac = (size_t)D.adapt_cap;
   void* ad_A = cv.take<char>(ac * D.d * es);
+  void* ad_At = cv.take<char>(ac > 0 && es == 2 ? (size_t)D.d * 64 * es : 0);
   float* ad_Z = cv.take<float>(ac * D.Vd * 4);
   float* ad_Z0 = cv.take<float>(ac * D.Vd * 4);
   float* ad_part = cv.take<float>(ac * D.n_chunks_d * kVocabRec10 * 4);
   float* ad_part0 = cv.take<float>(ac * D.n_chunks_d * 5 * 4);
+  float* ad_stat = cv.take<float>(ac * kAdaptStat * 4);
   float* ad_psi = cv.take<float>(ac * SB_PSI_DIM * 4);
   float* ad_ds = cv.take<float>(ac * 4 * 4);
   float* ad_loss = cv.take<float>(ac * 4);
@@ -309,8 +313,8 @@ static size_t layout(const Dims& D, void* base, sb_ctx* c) {
     c->logits = logits;
     c->node_stats = node_stats;
     c->row_lse = row_lse;
-    c->ad = AdaptBufs{ad_A, ad_Z, ad_Z0, ad_part, ad_part0, ad_psi, ad_ds,
-                      ad_loss, ad_n};
+    c->ad = AdaptBufs{ad_A, ad_At, ad_Z, ad_Z0, ad_part, ad_part0, ad_stat,
+                      ad_psi, ad_ds, ad_loss, ad_n};
     c->vpart = vpart;
     c->cond_buf = cond_buf;
     c->taps_pf = taps_pf;
@@ -1384,9 +1388,9 @@ int head_update_impl(sb_ctx* c, sb_adapt_buffer* buf, const void* lm_head0,
   launch_vocab_partial(a.Z0, a.n, cap, D.Vd, D.n_chunks_d, 1, a.part0, st);
   launch_adapt_rows(a.Z, a.Z0, D.Vd, a.part, a.part0, n_chunks, a.n, cap,
                     buf->h, D.d, buf->target, c->dw.d2t, w->rank_w, w->rank_b,
-                    kl_weight, a.psi, a.ds, a.loss, st);
-  launch_lm_update<T>(static_cast<T*>(w->lm_head), D.Vd, D.d, a.Z, A, a.n, lr,
-                      st);
+                    kl_weight, a.stat, a.psi, a.ds, a.loss, st);
+  launch_lm_update<T>(static_cast<T*>(w->lm_head), D.Vd, D.d, a.Z, A,
+                      static_cast<T*>(a.At), a.n, lr, st);
   launch_rank_update(w->rank_w, w->rank_b, a.ds, buf->h, a.psi, D.d, a.n, lr,
                      a.loss, loss_out, buf->count, st);
   return hip_check(c, "sb_head_update");

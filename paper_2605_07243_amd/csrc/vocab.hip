@@ -503,53 +503,58 @@ void launch_verify_finalize(const float* part, int n_chunks, const int* n,
                                               argmax);
 }
 
-// Head-only drafter update (Sec. 3.4), one workgroup per buffered position
-// i: the drafter distribution p = softmax(z), z = W_train a (chunk records
-// part), and p0 = softmax(z0), z0 = W_0 a (records part0); psi of p; the
-// target's drafter id and rank in p, whose bucket is the rank-head label
-// (past rank 10, or outside the drafter vocabulary: b3); KL(p || p0); the
-// LM-logit gradient (1/n) [(p - e_y) + kl_w p (log p - log p0 - KL)]
-// written over z; the rank-head score gradient
-// ds = (1/n) (softmax(W_r [h, psi] + b_r) - e_label); the position's loss.
-__global__ __launch_bounds__(256) void adapt_row_kernel(
-    float* __restrict__ Z, const float* __restrict__ Z0, int Vd,
+// Head-only drafter update (Sec. 3.4), per buffered position i: the drafter
+// distribution p = softmax(z), z = W_train a (chunk records part), and
+// p0 = softmax(z0), z0 = W_0 a (records part0); psi of p; the target's
+// drafter id y and rank in p, whose bucket is the rank-head label (past rank
+// 10, or outside the drafter vocabulary: b3); KL(p || p0); the LM-logit
+// gradient (1/n) [(p - e_y) + kl_w p (log p - log p0 - KL)] written over z;
+// the rank-head score gradient ds = (1/n) (softmax(W_r [h, psi] + b_r) -
+// e_label); the position's loss.
+//
+// Two launches of kAdaptParts workgroups per position (one workgroup per
+// position left 64 of 256 CUs two passes over 128256 logits each: 336 us for
+// 64 positions): the first sums each part of KL and of the rank, the second
+// adds the parts in order and writes the gradient of its part; one more
+// workgroup per position takes psi, the rank head and the loss.
+// stat[i]: lse, lse0, z[y], y (int bits), then the parts of KL, of the rank.
+__global__ __launch_bounds__(256) void adapt_kl_kernel(
+    const float* __restrict__ Z, const float* __restrict__ Z0, int Vd,
     const float* __restrict__ part, const float* __restrict__ part0,
-    int n_chunks, const int* __restrict__ n_eff, const float* __restrict__ h,
-    int d, const int* __restrict__ targets, const int* __restrict__ d2t,
-    const float* __restrict__ rank_w, const float* __restrict__ rank_b,
-    float kl_w, float* __restrict__ psi_out, float* __restrict__ ds_out,
-    float* __restrict__ loss_out) {
-  __shared__ float psi_s[SB_PSI];
+    int n_chunks, const int* __restrict__ n_eff,
+    const int* __restrict__ targets, const int* __restrict__ d2t,
+    float* __restrict__ stat) {
   __shared__ float red[4];
-  __shared__ float sh_lse, sh_lse0, sh_zy;
+  __shared__ float sh[3];
   __shared__ int sh_y;
-  const int i = blockIdx.x;
-  const int n = *n_eff;
-  if (i >= n) return;
-  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-  float* z = Z + (size_t)i * Vd;
-  const float* z0 = Z0 + (size_t)i * Vd;
+  const int c = blockIdx.x, i = blockIdx.y;
+  if (i >= *n_eff) return;
+  const int tid = threadIdx.x;
+  const float* z = Z + (size_t)i * Vd;
+  const float4* z4 = reinterpret_cast<const float4*>(z);   // Vd % 64 == 0
+  const float4* z04 = reinterpret_cast<const float4*>(Z0 + (size_t)i * Vd);
+  const int per = (Vd / 4 + kAdaptParts - 1) / kAdaptParts;
+  const int v0 = c * per, v1 = min(Vd / 4, v0 + per);
+  // the first four float4 of each array on their way before the merge
+  float4 a[4], a0[4];
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const int v = min(v0 + tid + 256 * q, Vd / 4 - 1);
+    a[q] = z4[v];
+    a0[q] = z04[v];
+  }
   if (tid < 64) {
-    float bv[SB_TOPK_K];
-    int bi[SB_TOPK_K];
-    float M, S, U;
-    merge_row<SB_TOPK_K>(part + (size_t)i * n_chunks * (2 * SB_TOPK_K + 3),
-                         n_chunks, bv, bi, M, S, U);
-    float bv0[1];
-    int bi0[1];
-    float M0, S0, U0;
-    merge_row<1>(part0 + (size_t)i * n_chunks * 5, n_chunks, bv0, bi0, M0, S0,
-                 U0);
+    float m = -FLT_MAX, s = 0.f, u = 0.f, m0 = -FLT_MAX, s0 = 0.f, u0 = 0.f;
+    for (int k = tid; k < n_chunks; k += 64) {
+      const float* o = part + ((size_t)i * n_chunks + k) * (2 * SB_TOPK_K + 3) +
+                       2 * SB_TOPK_K;
+      const float* o0 = part0 + ((size_t)i * n_chunks + k) * 5 + 2;
+      stats_merge(m, s, u, o[0], o[1], 0.f);
+      stats_merge(m0, s0, u0, o0[0], o0[1], 0.f);
+    }
+    wave_stats(m, s, u);
+    wave_stats(m0, s0, u0);
     if (tid == 0) {
-      const float lse = M + logf(S);
-      for (int k = 0; k < SB_TOPK_K; ++k) psi_s[k] = bv[k] - lse;
-      psi_s[10] = bv[0] - bv[1];
-      psi_s[11] = bv[0] - bv[2];
-      psi_s[12] = bv[0] - bv[4];
-      psi_s[13] = __expf(bv[0] - lse);
-      psi_s[14] = lse - U / S;
-      sh_lse = lse;
-      sh_lse0 = M0 + logf(S0);
       // the target's drafter id (d2t strictly increasing), -1 if absent
       const int t = targets[i];
       int y = -1;
@@ -568,38 +573,108 @@ __global__ __launch_bounds__(256) void adapt_row_kernel(
           else hi = mid - 1;
         }
       }
+      sh[0] = m + logf(s);
+      sh[1] = m0 + logf(s0);
+      sh[2] = y >= 0 ? z[y] : 0.f;
       sh_y = y;
-      sh_zy = y >= 0 ? z[y] : 0.f;
     }
   }
   __syncthreads();
-  const float lse = sh_lse, lse0 = sh_lse0, zy = sh_zy;
+  const float lse = sh[0], lse0 = sh[1], zy = sh[2];
   const int y = sh_y;
-  // pass 1: KL(p || p0) and the target's rank
   float kl = 0.f, above = 0.f;
-  for (int v = tid; v < Vd; v += 256) {
-    const float zv = z[v];
-    const float lp = zv - lse, lp0 = z0[v] - lse0;
+  auto one = [&](float zv, float z0v, int id) {
+    const float lp = zv - lse, lp0 = z0v - lse0;
     kl += __expf(lp) * (lp - lp0);
-    if (y >= 0 && (zv > zy || (zv == zy && v < y))) above += 1.f;
-  }
+    if (y >= 0 && (zv > zy || (zv == zy && id < y))) above += 1.f;
+  };
+  auto four = [&](float4 x, float4 x0, int v) {
+    one(x.x, x0.x, 4 * v);
+    one(x.y, x0.y, 4 * v + 1);
+    one(x.z, x0.z, 4 * v + 2);
+    one(x.w, x0.w, 4 * v + 3);
+  };
+#pragma unroll
+  for (int q = 0; q < 4; ++q)
+    if (v0 + tid + 256 * q < v1) four(a[q], a0[q], v0 + tid + 256 * q);
+  for (int v = v0 + tid + 1024; v < v1; v += 256) four(z4[v], z04[v], v);
   kl = block_sum(kl, red);
   above = block_sum(above, red);
-  const float inv_n = 1.0f / (float)n;
-  // pass 2: the LM-logit gradient over z
-  for (int v = tid; v < Vd; v += 256) {
-    const float lp = z[v] - lse, lp0 = z0[v] - lse0;
-    const float p = __expf(lp);
-    // no cross-entropy term (and so no p term) for a target outside the
-    // drafter vocabulary
-    float g = y >= 0 ? p - (v == y ? 1.f : 0.f) : 0.f;
-    g += kl_w * p * (lp - lp0 - kl);
-    z[v] = g * inv_n;
+  if (tid == 0) {
+    float* o = stat + (size_t)i * kAdaptStat;
+    o[4 + c] = kl;
+    o[4 + kAdaptParts + c] = above;
+    if (c == 0) {
+      o[0] = lse;
+      o[1] = lse0;
+      o[2] = zy;
+      o[3] = __int_as_float(y);
+    }
   }
-  // rank head over [h, psi]
+}
+
+__global__ __launch_bounds__(256) void adapt_grad_kernel(
+    float* __restrict__ Z, const float* __restrict__ Z0, int Vd,
+    const float* __restrict__ part, int n_chunks,
+    const int* __restrict__ n_eff, const float* __restrict__ h, int d,
+    const float* __restrict__ rank_w, const float* __restrict__ rank_b,
+    float kl_w, const float* __restrict__ stat, float* __restrict__ psi_out,
+    float* __restrict__ ds_out, float* __restrict__ loss_out) {
+  __shared__ float psi_s[SB_PSI];
+  __shared__ float red[4];
+  const int c = blockIdx.x, i = blockIdx.y;
+  const int n = *n_eff;
+  if (i >= n) return;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const float* st = stat + (size_t)i * kAdaptStat;
+  const float lse = st[0], lse0 = st[1], zy = st[2];
+  const int y = __float_as_int(st[3]);
+  const float kl = wave_sum(lane < kAdaptParts ? st[4 + lane] : 0.f);
+  const float inv_n = 1.0f / (float)n;
+  if (c < kAdaptParts) {
+    // the LM-logit gradient over z
+    float4* z4 = reinterpret_cast<float4*>(Z + (size_t)i * Vd);
+    const float4* z04 = reinterpret_cast<const float4*>(Z0 + (size_t)i * Vd);
+    const int per = (Vd / 4 + kAdaptParts - 1) / kAdaptParts;
+    const int v0 = c * per, v1 = min(Vd / 4, v0 + per);
+    auto grad = [&](float zv, float z0v, int id) {
+      const float lp = zv - lse, lp0 = z0v - lse0;
+      const float p = __expf(lp);
+      // no cross-entropy term (and so no p term) for a target outside the
+      // drafter vocabulary
+      float g = y >= 0 ? p - (id == y ? 1.f : 0.f) : 0.f;
+      g += kl_w * p * (lp - lp0 - kl);
+      return g * inv_n;
+    };
+#pragma unroll 4
+    for (int v = v0 + tid; v < v1; v += 256) {
+      const float4 x = z4[v], x0 = z04[v];
+      z4[v] = make_float4(grad(x.x, x0.x, 4 * v), grad(x.y, x0.y, 4 * v + 1),
+                          grad(x.z, x0.z, 4 * v + 2), grad(x.w, x0.w, 4 * v + 3));
+    }
+    return;
+  }
+  // psi, the rank head over [h, psi] and the loss
+  if (tid < 64) {
+    float bv[SB_TOPK_K];
+    int bi[SB_TOPK_K];
+    float M, S, U;
+    merge_row<SB_TOPK_K>(part + (size_t)i * n_chunks * (2 * SB_TOPK_K + 3),
+                         n_chunks, bv, bi, M, S, U);
+    if (tid == 0) {
+      for (int k = 0; k < SB_TOPK_K; ++k) psi_s[k] = bv[k] - lse;
+      psi_s[10] = bv[0] - bv[1];
+      psi_s[11] = bv[0] - bv[2];
+      psi_s[12] = bv[0] - bv[4];
+      psi_s[13] = __expf(bv[0] - lse);
+      psi_s[14] = lse - U / S;
+    }
+  }
+  __syncthreads();
   const float* hr = h + (size_t)i * d;
   const int ld = d + SB_PSI;
   float acc[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll 4
   for (int j = tid; j < ld; j += 256) {
     const float x = j < d ? hr[j] : psi_s[j - d];
 #pragma unroll
@@ -608,6 +683,8 @@ __global__ __launch_bounds__(256) void adapt_row_kernel(
   float sc[4];
 #pragma unroll
   for (int b = 0; b < 4; ++b) sc[b] = block_sum(acc[b], red) + rank_b[b];
+  const float above =
+      wave_sum(lane < kAdaptParts ? st[4 + kAdaptParts + lane] : 0.f);
   if (tid == 0) {
     const int r = (int)above + 1;
     const int label = y < 0 ? 3 : (r == 1 ? 0 : r <= 4 ? 1 : r <= 10 ? 2 : 3);
@@ -629,12 +706,14 @@ void launch_adapt_rows(float* Z, const float* Z0, int Vd, const float* part,
                        const float* part0, int n_chunks, const int* n_eff,
                        int cap, const float* h, int d, const int* targets,
                        const int* d2t, const float* rank_w,
-                       const float* rank_b, float kl_w, float* psi_out,
-                       float* ds_out, float* loss_out, hipStream_t st) {
-  adapt_row_kernel<<<cap, 256, 0, st>>>(Z, Z0, Vd, part, part0, n_chunks,
-                                        n_eff, h, d, targets, d2t, rank_w,
-                                        rank_b, kl_w, psi_out, ds_out,
-                                        loss_out);
+                       const float* rank_b, float kl_w, float* stat,
+                       float* psi_out, float* ds_out, float* loss_out,
+                       hipStream_t st) {
+  adapt_kl_kernel<<<dim3(kAdaptParts, cap), 256, 0, st>>>(
+      Z, Z0, Vd, part, part0, n_chunks, n_eff, targets, d2t, stat);
+  adapt_grad_kernel<<<dim3(kAdaptParts + 1, cap), 256, 0, st>>>(
+      Z, Z0, Vd, part, n_chunks, n_eff, h, d, rank_w, rank_b, kl_w, stat,
+      psi_out, ds_out, loss_out);
 }
 
 }  // namespace sb
