@@ -362,8 +362,8 @@ int sb_accept_sample(sb_ctx* ctx, int32_t n_seqs, const sb_tree* tree,
 /* Allocation-free variant of sb_accept_sample, for callers that cannot
  * allocate (code under HIP graph capture, tight serving loops, harnesses
  * that forbid allocation): same arguments, same results, but the per-node
- * softmax tile statistics live in a static device array of the library
- * (65536 float2 entries, 512 KiB, one copy per GPU, held until the process
+ * softmax block statistics live in a static device array of the library
+ * (65536 tiles of 16384 tokens, 16 MiB, one copy per GPU, held until the process
  * ends) instead of the bound workspace, and the call allocates nothing.
  * The context need not be bound unless out->r_reject is requested (the
  * signal reads the drafter weights and the workspace); only its

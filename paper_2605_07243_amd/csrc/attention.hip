@@ -1008,6 +1008,7 @@ void launch_tree_attn(const T* q, const CallPlan& p, const KVView& kv,
       // (balanced: 83 vs 66 us)
       const int gx = a.groups * Hkv;
       const bool bal = split_rows != nullptr && p.n_seqs <= 64 &&
+                       rows_per_seq_cap * (H / Hkv) > 32 &&
                        p.n_seqs * gx <= kAttnSlots && max_prefix <= 256 * 64 &&
                        (p.n_seqs == 1 ||          // even splits, no rounding
                         (long)p.n_seqs * gx * n_split > kAttnSlots);
@@ -1086,9 +1087,13 @@ int attn_qgroups(int rows_per_seq_cap, int G, int seq_heads, int es) {
 // 16-row kernel: two rounds (its workgroups are smaller; at one sequence of
 // 60 nodes the splits stay at 128 keys or more, see the caller).
 int attn_workgroup_target(int rows_per_seq_cap, int G, int seq_heads, int es) {
-  return attn_shape(rows_per_seq_cap, G, seq_heads, es).mfma32
-             ? kAttnSlots
-             : 2 * kAttnSlots;
+  if (!attn_shape(rows_per_seq_cap, G, seq_heads, es).mfma32)
+    return 2 * kAttnSlots;
+  // at most 32 query vectors per KV head (catch-up rows, first blocks of many
+  // sequences): partials are small, and two workgroups of four waves fit a
+  // CU, so the prefix is cut for 512 (16 sequences x 1 row over 512-2048 keys:
+  // 41 us for 256 workgroups, 38 for 512, 55 for 1024)
+  return rows_per_seq_cap * G <= 32 ? 2 * kAttnSlots : kAttnSlots;
 }
 
 template void launch_tree_attn<float>(const float*, const CallPlan&,

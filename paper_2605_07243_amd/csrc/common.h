@@ -170,6 +170,14 @@ __device__ __forceinline__ int xcd_grouped(int b, int total) {
   return x * q + min(x, r) + (b >> 3);
 }
 
+// Orders a wave's LDS accesses before and after it (its lanes run in step,
+// so this only keeps the compiler from moving them).
+__device__ __forceinline__ void wave_lds_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // Larger (value, smaller id) first.
 __device__ __forceinline__ bool better(float v, int id, float bv, int bid) {
   return v > bv || (v == bv && id < bid);

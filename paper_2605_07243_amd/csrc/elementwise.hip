@@ -353,17 +353,32 @@ __global__ __launch_bounds__(256) void qkv_post_kernel(
       return;
     }
   }
-  // the page (of the segment pool, or of the cache) and slot of the row's K/V
-  const bool paged = p.kv_row != nullptr;
-  const int seq = p.seq[i], slot = paged ? p.kv_dst[i] : p.slot[i];
-  const int sl = slot & 15;
-  const size_t page_base =
-      paged ? (size_t)checked_index(
-                  kv.page_table[(size_t)seq * kv.max_pages + (slot >> 4)],
-                  kv.n_pages, kv.err, kDevPage)
-            : (size_t)seq * kv.seg_pages + (slot >> 4);
-  T* kd = static_cast<T*>(paged ? kv.k : kv.seg_k);
-  T* vd = static_cast<T*>(paged ? kv.v : kv.seg_v);
+  // where the row's K/V go: segment slot and / or cache entry (one outside
+  // the page table is not written: a sequence may have outgrown its table)
+  const int seq = p.seq[i];
+  T* kseg = nullptr;
+  T* vseg = nullptr;
+  T* kcache = nullptr;
+  T* vcache = nullptr;
+  int sl = 0, cl = 0;
+  if (p.kv_row == nullptr) {
+    const int slot = p.slot[i];
+    const size_t page = ((size_t)seq * kv.seg_pages + (slot >> 4)) * Hkv;
+    sl = slot & 15;
+    kseg = static_cast<T*>(kv.seg_k) + page * 16 * hd;
+    vseg = static_cast<T*>(kv.seg_v) + page * 16 * hd;
+  }
+  if (p.kv_row != nullptr || p.write_through) {
+    const int e = p.kv_dst[i];
+    if (e >= 0 && (e >> 4) < kv.max_pages) {
+      const size_t page =
+          (size_t)checked_index(kv.page_table[(size_t)seq * kv.max_pages + (e >> 4)],
+                                kv.n_pages, kv.err, kDevPage) * Hkv;
+      cl = e & 15;
+      kcache = static_cast<T*>(kv.k) + page * 16 * hd;
+      vcache = static_cast<T*>(kv.v) + page * 16 * hd;
+    }
+  }
   const double pos = (double)p.pos[i];
   for (int t = threadIdx.x; t < half; t += blockDim.x) {
     // angle in double, reduced to [-pi, pi] before the fp32 sincos
@@ -384,16 +399,30 @@ __global__ __launch_bounds__(256) void qkv_post_kernel(
                                   a.z * c4.z - b.z * s4.z, a.w * c4.w - b.w * s4.w);
     const float4 rb = make_float4(b.x * c4.x + a.x * s4.x, b.y * c4.y + a.y * s4.y,
                                   b.z * c4.z + a.z * s4.z, b.w * c4.w + a.w * s4.w);
-    T* dst = head < H ? q + ((size_t)i * H + head) * hd
-                      : kd + ((page_base * Hkv + (head - H)) * 16 + sl) * hd;
-    store4<T>(dst + j, ra);
-    store4<T>(dst + j + half, rb);
+    if (head < H) {
+      T* dst = q + ((size_t)i * H + head) * hd + j;
+      store4<T>(dst, ra);
+      store4<T>(dst + half, rb);
+      return;
+    }
+    if (kseg != nullptr) {
+      T* dst = kseg + ((head - H) * 16 + sl) * hd + j;
+      store4<T>(dst, ra);
+      store4<T>(dst + half, rb);
+    }
+    if (kcache != nullptr) {
+      T* dst = kcache + ((head - H) * 16 + cl) * hd + j;
+      store4<T>(dst, ra);
+      store4<T>(dst + half, rb);
+    }
   } else if (idx < n_items) {
-    T* dv = vd + ((page_base * Hkv + head) * hd + j) * 16 + sl;
-    dv[0] = Elem<T>::from_f32(a.x);
-    dv[16] = Elem<T>::from_f32(a.y);
-    dv[32] = Elem<T>::from_f32(a.z);
-    dv[48] = Elem<T>::from_f32(a.w);
+    const T v[4] = {Elem<T>::from_f32(a.x), Elem<T>::from_f32(a.y),
+                    Elem<T>::from_f32(a.z), Elem<T>::from_f32(a.w)};
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      if (vseg != nullptr) vseg[(head * hd + j + e) * 16 + sl] = v[e];
+      if (vcache != nullptr) vcache[(head * hd + j + e) * 16 + cl] = v[e];
+    }
   }
 }
 

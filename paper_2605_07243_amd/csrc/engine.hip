@@ -153,7 +153,7 @@ struct sb_ctx {
   float* ml = nullptr;
   int* split_rows = nullptr;     // [R] attention splits of each row's sequence
   float* logits = nullptr;
-  float2* node_stats = nullptr;  // [S][budget][tiles] softmax stats of z / T
+  SampleStat* node_stats = nullptr;  // [S][budget][blocks] softmax stats of z / T
   float* row_lse = nullptr;      // [S][row_cap] drafter rows' log-sum-exp
   AdaptBufs ad{};                // head-update workspace
   float* vpart = nullptr;
@@ -252,8 +252,8 @@ static size_t layout(const Dims& D, void* base, sb_ctx* c) {
   float* ad_ds = cv.take<float>(ac * 4 * 4);
   float* ad_loss = cv.take<float>(ac * 4);
   int* ad_n = cv.take<int>(4);
-  float2* node_stats = cv.take<float2>((size_t)D.S * D.budget *
-                                       sample_tiles(D.V) * 8);
+  SampleStat* node_stats = cv.take<SampleStat>(
+      sample_scratch(D.S, D.budget, sample_blocks(D.V)) * sizeof(SampleStat));
   float* vpart = cv.take<float>((size_t)D.R_dec *
                                  std::max(D.n_chunks, D.n_chunks_f) *
                                  kVocabRec10 * 4);
@@ -1009,28 +1009,25 @@ int commit_impl(sb_ctx* c, sb_seqs* sq, const sb_tree* t,
                 sb_kv* tkv, sb_kv* dkv, hipStream_t st) {
   const Dims& D = c->D;
   const TreeDims td = tree_dims(c, sq->n_seqs);
-  launch_commit_plan(td, *t, *acc, sq->T, c->ci, c->fb, c->taps_idx, c->n_aux,
+  CallPlan fb = c->fb;
+  fb.write_through = true;
+  launch_commit_plan(td, *t, *acc, sq->T, c->ci, fb, c->taps_idx, c->n_aux,
                      st);
   const KVPools tp{tkv->k, tkv->v, tkv->page_table, c->cfg.max_pages,
                    tkv->n_pages, c->tseg_k, c->tseg_v, D.tpages, c->dbg()};
   const KVPools dp{dkv->k, dkv->v, dkv->page_table, c->cfg.max_pages,
                    dkv->n_pages, c->dseg_k, c->dseg_v, D.dpages, c->dbg()};
-  launch_commit_copy<T>(td, *t, *acc, c->ci, false, tp, D.S, D.L, D.Hkv, D.hd,
-                        st);
-  launch_commit_copy<T>(td, *t, *acc, c->ci, true, dp, D.S, D.LD, D.Hkv, D.hd,
-                        st);
+  launch_commit_apply<T>(td, *t, *acc, c->ci, tp, D.L, dp, D.LD, D.S, D.Hkv,
+                         D.hd, *sq, v->taps, st);
   // catch-up rows where the tree has no row continuing the accepted path
   // (usually none: its launches test the live count before loading)
   set_rows_likely_empty(true);
   cond_rows<T>(c, v->taps, c->taps_idx, c->n_aux, D.S, st);
   const Prefix pf{dkv, c->dseg_k, c->dseg_v, D.dpages};
-  CallPlan fb = c->fb;
   fb.n_seqs = sq->n_seqs;
   fb.cap = sq->n_seqs;
   drafter_forward<T>(c, fb, c->cond_buf, pf, 1, false, st);
   set_rows_likely_empty(false);
-  launch_seg_to_cache<T>(fb, dp, D.S, D.LD, D.Hkv, D.hd, st);
-  launch_commit_state(td, *sq, *acc, c->ci, v->taps, st);
   if (c->T_bound > 0) c->T_bound += D.M * D.K + 1;
   return hip_check(c, "sb_commit");
 }
@@ -1200,20 +1197,12 @@ int sb_tree_verify(sb_ctx* c, const sb_seqs* seqs, const sb_tree* tree,
 
 namespace {
 
-// The verifier-derived signal of sb_accept / sb_accept_sample, when asked.
-void reject_signal(sb_ctx* c, int n_seqs, const sb_tree& t,
-                   const sb_accept_out& o, hipStream_t st) {
-  if (o.r_reject == nullptr) return;
-  const float eps = c->cfg.target.norm_eps;
-  const float* g = static_cast<const float*>(c->dw.final_norm);
-  if (is_bf16(c))
-    launch_reject_signal<bf16_t>(tree_dims(c, n_seqs), t, o, c->row_lse,
-                                 static_cast<const bf16_t*>(c->dw.lm_head), g,
-                                 eps, c->dw.d2t, c->D.Vd, o.r_reject, st);
-  else
-    launch_reject_signal<float>(tree_dims(c, n_seqs), t, o, c->row_lse,
-                                static_cast<const float*>(c->dw.lm_head), g,
-                                eps, c->dw.d2t, c->D.Vd, o.r_reject, st);
+// Inputs of the verifier-derived signal of sb_accept / sb_accept_sample
+// (computed when o.r_reject is asked for).
+SignalArgs signal_args(sb_ctx* c, const sb_accept_out& o) {
+  return SignalArgs{c->row_lse, c->dw.lm_head,
+                    static_cast<const float*>(c->dw.final_norm),
+                    c->cfg.target.norm_eps, c->dw.d2t, c->D.Vd, o.r_reject};
 }
 
 }  // namespace
@@ -1231,8 +1220,8 @@ int sb_accept(sb_ctx* c, int32_t n_seqs, const sb_tree* tree,
       bad_ptr(out->n_accepted, 4) || bad_ptr(out->bonus, 4) ||
       (out->r_reject && bad_ptr(out->r_reject, 4)))
     return fail(c, SB_EINVAL, "accept pointer NULL or misaligned");
-  launch_accept(tree_dims(c, n_seqs), *tree, argmax, *out, S_(stream));
-  reject_signal(c, n_seqs, *tree, *out, S_(stream));
+  launch_accept(tree_dims(c, n_seqs), *tree, argmax, *out,
+                signal_args(c, *out), is_bf16(c), S_(stream));
   return hip_check(c, "sb_accept");
 }
 
@@ -1256,21 +1245,22 @@ int sb_accept_sample(sb_ctx* c, int32_t n_seqs, const sb_tree* tree,
                                   std::to_string(sample_max_vocab()));
   const hipStream_t st = S_(stream);
   const float inv_t = 1.0f / temperature;
-  launch_node_stats(logits, c->D.V, inv_t, tree->n_nodes, n_seqs, c->D.budget,
-                    c->node_stats, st);
   launch_accept_sample(tree_dims(c, n_seqs), *tree, logits, c->D.V, inv_t,
-                       c->node_stats, u_accept, u_bonus, *out, st);
-  reject_signal(c, n_seqs, *tree, *out, st);
+                       c->node_stats, u_accept, u_bonus, *out,
+                       signal_args(c, *out), is_bf16(c), st);
   return hip_check(c, "sb_accept_sample");
 }
 
 }  // extern "C"
 
 // Scratch of the allocation-free stochastic acceptance: the per-node
-// softmax tile statistics that sb_accept_sample keeps in the workspace.
+// softmax block statistics that sb_accept_sample keeps in the workspace.
 // Every GPU holds its own copy at its own address until the process ends.
-constexpr size_t kNoAllocStats = 65536;   // float2 entries, 512 KiB
-static __device__ __align__(256) float2 scratch[kNoAllocStats];
+constexpr size_t kNoAllocTiles = 65536;   // of 16384 tokens: 16 MiB
+constexpr size_t kNoAllocStats =
+    kNoAllocTiles * (16384 / kSampleBlock) +
+    (SB_MAX_SEQS * sizeof(SampleWalk) + sizeof(SampleStat)) / sizeof(SampleStat);
+static __device__ __align__(256) SampleStat scratch[kNoAllocStats];
 
 namespace {
 
@@ -1280,7 +1270,7 @@ void* g_scratch_ptr[kMaxDevices] = {};   // device address of scratch per GPU
 
 // Device address of this GPU's scratch, resolved once per device with the
 // device current (host code never passes the array's own name).
-int scratch_for_current_device(sb_ctx* c, float2** out) {
+int scratch_for_current_device(sb_ctx* c, SampleStat** out) {
   int dev = -1;
   if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kMaxDevices)
     return fail(c, SB_EHIP, "sb_accept_sample_noalloc: hipGetDevice failed");
@@ -1294,7 +1284,7 @@ int scratch_for_current_device(sb_ctx* c, float2** out) {
                       hipGetErrorString(e));
     g_scratch_ptr[dev] = ptr;
   }
-  *out = static_cast<float2*>(g_scratch_ptr[dev]);
+  *out = static_cast<SampleStat*>(g_scratch_ptr[dev]);
   return SB_OK;
 }
 
@@ -1323,21 +1313,19 @@ int sb_accept_sample_noalloc(sb_ctx* c, int32_t n_seqs, const sb_tree* tree,
   if (c->D.V > sample_max_vocab())
     return fail(c, SB_ESHAPE, "sb_accept_sample_noalloc supports vocab <= " +
                                   std::to_string(sample_max_vocab()));
-  const size_t need = (size_t)n_seqs * c->D.budget * sample_tiles(c->D.V);
-  if (need > kNoAllocStats)
+  const size_t need = (size_t)n_seqs * c->D.budget * ((c->D.V + 16383) / 16384);
+  if (need > kNoAllocTiles)
     return fail(c, SB_EBUDGET,
                 "sb_accept_sample_noalloc: n_seqs * budget * ceil(vocab / "
                 "16384) = " + std::to_string(need) + " exceeds its static "
-                "scratch of " + std::to_string(kNoAllocStats) + " entries");
-  float2* stats = nullptr;
+                "scratch of " + std::to_string(kNoAllocTiles) + " tiles");
+  SampleStat* stats = nullptr;
   if ((rc = scratch_for_current_device(c, &stats))) return rc;
   const hipStream_t st = S_(stream);
   const float inv_t = 1.0f / temperature;
-  launch_node_stats(logits, c->D.V, inv_t, tree->n_nodes, n_seqs, c->D.budget,
-                    stats, st);
   launch_accept_sample(tree_dims(c, n_seqs), *tree, logits, c->D.V, inv_t,
-                       stats, u_accept, u_bonus, *out, st);
-  reject_signal(c, n_seqs, *tree, *out, st);
+                       stats, u_accept, u_bonus, *out, signal_args(c, *out),
+                       is_bf16(c), st);
   return hip_check(c, "sb_accept_sample_noalloc");
 }
 

@@ -35,6 +35,9 @@ struct CallPlan {
   // prefix_len counts the piece's own keys too, K/V go straight to cache
   // entry kv_dst, and a row attends to the entries up to its own.
   int* kv_row = nullptr;
+  // Catch-up rows of a commit: K/V go to the segment and to cache entry
+  // kv_dst.
+  bool write_through = false;
   int cap;
   int vis_words;
   int n_seqs;        // host value: sequences with valid seq_off entries
@@ -124,7 +127,8 @@ template <typename T>
 void launch_norm_rows(const T* src, int n_rows, int d, const float* g,
                       float eps, T* out, hipStream_t st);
 // K/V rows go to the segment pool of kv (slot p.slot of sequence p.seq), or,
-// for a causal plan (p.kv_row), to entry p.kv_dst of the paged cache.
+// for a causal plan (p.kv_row), to entry p.kv_dst of the paged cache, or to
+// both (p.write_through).
 template <typename T>
 void launch_qkv_post(const float* P, int ks, size_t part_stride,
                      const CallPlan& p, int H, int Hkv, int hd, float theta,
@@ -248,13 +252,17 @@ void launch_attach(const TreeDims& td, const sb_tree& t, const sb_draft_out& o,
                    const int* blk_row0, const int* blk_nst, hipStream_t st);
 void launch_plan_verify(const TreeDims& td, const sb_tree& t, const int* T,
                         const CallPlan& p, hipStream_t st);
-// Verifier-derived signal at the rejected position (tree.hip).
-template <typename T>
-void launch_reject_signal(const TreeDims& td, const sb_tree& t,
-                          const sb_accept_out& acc, const float* row_lse,
-                          const T* lm_head, const float* gain, float eps,
-                          const int* d2t, int Vd, float* r_out,
-                          hipStream_t st);
+// Inputs of the verifier-derived signal at the rejected position, and its
+// output r [S] (null: not asked for); lm_head in the weights' element type.
+struct SignalArgs {
+  const float* row_lse;
+  const void* lm_head;
+  const float* gain;
+  float eps;
+  const int* d2t;
+  int Vd;
+  float* r;
+};
 // Head-only drafter update (tree.hip push, vocab.hip rows, adapt.hip).
 void launch_adapt_push(const TreeDims& td, const sb_tree& t,
                        const sb_accept_out& acc, float* buf_h, int* buf_y,
@@ -284,33 +292,41 @@ void launch_rank_update(float* rank_w, float* rank_b, const float* ds,
 int adapt_column_width(int elem_bytes);
 int adapt_stripe_rows();
 // Stochastic acceptance (sampling.hip).
-int sample_tiles(int V);       // statistics tiles per node row
+constexpr int kSampleBlock = 1024;   // tokens per statistics block
+struct SampleStat {
+  double s;      // sum of exp(x - m), x = z / T
+  float m;       // maximum x
+  float pad;
+};
+// What the walk leaves for the draw when they are separate launches.
+struct SampleWalk {
+  int cur, leaf, nrej;
+  int rej[64];
+};
+int sample_blocks(int V);            // statistics blocks per node row
+// SampleStat entries that a call of these sizes uses (walk states included).
+size_t sample_scratch(int n_seqs, int budget, int n_blk);
 int sample_max_vocab();
-void launch_node_stats(const float* logits, int V, float inv_t,
-                       const int* n_nodes, int n_seqs, int budget,
-                       float2* stats, hipStream_t st);
 void launch_accept_sample(const TreeDims& td, const sb_tree& t,
                           const float* logits, int V, float inv_t,
-                          const float2* stats, const float* u_acc,
+                          SampleStat* stats, const float* u_acc,
                           const float* u_bonus, const sb_accept_out& o,
-                          hipStream_t st);
+                          const SignalArgs& g, bool bf16, hipStream_t st);
 void launch_accept(const TreeDims& td, const sb_tree& t, const int* argmax,
-                   const sb_accept_out& o, hipStream_t st);
+                   const sb_accept_out& o, const SignalArgs& g, bool bf16,
+                   hipStream_t st);
 void launch_commit_plan(const TreeDims& td, const sb_tree& t,
                         const sb_accept_out& acc, const int* T,
                         const CommitInfo& ci, const CallPlan& fb,
                         int* taps_idx, int* n_aux, hipStream_t st);
+// The committed K/V copies of both models (tl target and dl drafter layers)
+// and the new sequence state.
 template <typename T>
-void launch_commit_copy(const TreeDims& td, const sb_tree& t,
-                        const sb_accept_out& acc, const CommitInfo& ci,
-                        bool drafter, const KVPools& kv, int pool_seqs,
-                        int n_layers, int Hkv, int hd, hipStream_t st);
-template <typename T>
-void launch_seg_to_cache(const CallPlan& p, const KVPools& kv, int S,
-                         int n_layers, int Hkv, int hd, hipStream_t st);
-void launch_commit_state(const TreeDims& td, const sb_seqs& sq,
+void launch_commit_apply(const TreeDims& td, const sb_tree& t,
                          const sb_accept_out& acc, const CommitInfo& ci,
-                         const float* taps, hipStream_t st);
+                         const KVPools& tkv, int tl, const KVPools& dkv,
+                         int dl, int pool_seqs, int Hkv, int hd,
+                         const sb_seqs& sq, const float* taps, hipStream_t st);
 // Prefill passes (see prefill_impl): up to kPrefillRows prompt rows of any
 // sequences in one forward, cut into pieces of at most kPieceRows rows for
 // the attention.  Passed to the kernels by value.

@@ -10,18 +10,21 @@
 // is then distributed as the target's (speculative sampling applied
 // recursively over a node's candidates).
 //
-// Two launches.  First the softmax statistics (max, sum of exp) of z / T
-// for every verified node row, one workgroup per 16384-token tile of a row
-// so that a row is read by many CUs at once.  Then the walk, one workgroup
-// per sequence: wave 0 merges the tile statistics of the nodes it visits and
-// runs the tests; the whole workgroup does the residual draw, streaming the
-// last node's row tile by tile through LDS (coalesced loads) with each
-// thread owning 64 consecutive tokens of a tile, so that the cumulative
-// masses in token order are a scan over (tile, thread) in float64.
+// Two launches.  The first reads every verified node's row once and leaves,
+// per block of 1024 tokens, the maximum x and the sum of exp(x - maximum) of
+// x = z / T, the sum in float64 (bound by HBM: 613 rows of 128256 logits in
+// 53 us, 5.9 TB/s; reading only the rows that the walk visits, one workgroup
+// per sequence, took 123 us for the longest of 16 walks, as a CU reads a cold
+// row in about 12 us).  The second is one wave per sequence: a node's
+// log-sum-exp is a merge of its blocks, and the bonus draw scans the block
+// masses for the block that the target falls into, so that it reads 1024
+// logits of the row and not all of it (blocks that hold a rejected token are
+// summed again without it): 44 -> 12 us without the signal.
 #include <float.h>
 
 #include "common.h"
 #include "kernels.h"
+#include "signal.h"
 #include "specblock.h"
 
 namespace sb {
@@ -29,321 +32,449 @@ namespace sb {
 namespace {
 
 constexpr int kThreads = 256;
-constexpr int kTile = 16384;          // tokens per tile (64 per thread)
-constexpr int kMaxTiles = 16;         // V <= 262144
+constexpr int kTileBlocks = 16;       // blocks per workgroup of the first pass
+constexpr int kMaxBlocks = 256;       // V <= 262144
+constexpr int kLaneBlocks = kMaxBlocks / 64;
 constexpr int kMaxKids = 64;          // children tested per node (a node has
                                       // at most 2 * SB_TOPK: its continuing
                                       // row and the first row of a block
                                       // started at it)
 
-// Rows of sequences before s in call-row order (sequence-major, node order).
-__device__ __forceinline__ int row_offset(const int* __restrict__ n_nodes,
-                                          int s, int budget) {
-  int off = 0;
-  for (int j = 0; j < s; ++j) off += min(n_nodes[j], budget);
-  return off;
+__device__ __forceinline__ double wave_sum_d(double v) {
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, SB_WAVE);
+  return v;
 }
 
-__device__ __forceinline__ void stat_merge(float& m, float& s, float m2,
-                                           float s2) {
-  const float M = fmaxf(m, m2);
-  const float a = s > 0.f ? __expf(m - M) : 0.f;
-  const float b = s2 > 0.f ? __expf(m2 - M) : 0.f;
-  s = s * a + s2 * b;
-  m = M;
+// Rows of sequences before s in call-row order (sequence-major, node order);
+// called by a whole wave.
+__device__ __forceinline__ int row_offset(const int* __restrict__ n_nodes,
+                                          int s, int budget) {
+  const int lane = threadIdx.x & 63;
+  return wave_sum_i(lane < s ? min(n_nodes[lane], budget) : 0);
+}
+
+// A wave's 1024 tokens of a block, four float4 a lane; -FLT_MAX (exp = 0)
+// past the vocabulary.  QS: token stride between a lane's float4 (256: one
+// contiguous KiB per load; 4: sixteen consecutive tokens per lane).
+template <int QS>
+__device__ __forceinline__ void load_block(const float* __restrict__ z, int V,
+                                           int b, int lane, float4 (&v)[4]) {
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const int e = kSampleBlock * b + QS * q + (QS == 256 ? 4 : 16) * lane;
+    v[q] = e < V ? *reinterpret_cast<const float4*>(z + e)
+                 : make_float4(-FLT_MAX, -FLT_MAX, -FLT_MAX, -FLT_MAX);
+  }
+}
+
+// exp(x - ref) of a lane's sixteen consecutive tokens of a block, without the
+// rejected ones.
+__device__ __forceinline__ void block_probs(const float4 (&v)[4], float inv_t,
+                                            float ref, int x0, const int* rej,
+                                            int nrej, float (&p)[16]) {
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    p[4 * q] = __expf(v[q].x * inv_t - ref);
+    p[4 * q + 1] = __expf(v[q].y * inv_t - ref);
+    p[4 * q + 2] = __expf(v[q].z * inv_t - ref);
+    p[4 * q + 3] = __expf(v[q].w * inv_t - ref);
+  }
+#pragma unroll 1
+  for (int r = 0; r < nrej; ++r) {
+    const int x = rej[r] - x0;
+#pragma unroll
+    for (int i = 0; i < 16; ++i)
+      if (x == i) p[i] = 0.f;
+  }
 }
 
 }  // namespace
 
-// stats[(s * budget + n) * n_tiles + j] = (max, sum exp(x - max)) over the
-// tokens of tile j of node n's row, x = z * inv_t.
+// stats[(s * budget + n) * n_blk + b]: block b of node n's row.  One wave per
+// block, sixteen blocks per workgroup, all loads of a wave in flight.
+// ROWS: every node; the nodes that have children; or the one that the walk
+// ended at, if it has none.
+enum StatRows { kAllNodes, kInnerNodes, kLastLeaf };
+template <StatRows ROWS>
 __global__ __launch_bounds__(kThreads) void node_stats_kernel(
     const float* __restrict__ logits, int V, float inv_t,
-    const int* __restrict__ n_nodes, int budget, int n_tiles,
-    float2* __restrict__ stats) {
-  const int j = blockIdx.x, n = blockIdx.y, s = blockIdx.z;
-  if (n >= min(n_nodes[s], budget)) return;
+    const int* __restrict__ n_nodes, const int* __restrict__ parent, int budget,
+    int n_blk, const SampleWalk* __restrict__ walk,
+    SampleStat* __restrict__ stats) {
+  const int s = blockIdx.z;
+  const int nn = min(n_nodes[s], budget);
+  int n = blockIdx.y;
+  if constexpr (ROWS == kLastLeaf) {
+    if (!walk[s].leaf) return;
+    n = walk[s].cur;
+  }
+  if (n >= nn) return;
+  if constexpr (ROWS == kInnerNodes) {
+    bool kids = false;
+    for (int j = threadIdx.x; j < nn; j += kThreads)
+      kids |= parent[(size_t)s * budget + j] == n;
+    if (!__syncthreads_or(kids ? 1 : 0)) return;
+  }
   const float* z = logits + (size_t)(row_offset(n_nodes, s, budget) + n) * V;
-  const int base = j * kTile;
-  float4 v[16];
+  const int lane = threadIdx.x & 63;
+  const int b0 = blockIdx.x * kTileBlocks + (threadIdx.x >> 6);
+  float4 v[4][4];
 #pragma unroll
-  for (int q = 0; q < 16; ++q) {
-    const int e = base + 4 * (threadIdx.x + kThreads * q);
-    v[q] = e < V ? *reinterpret_cast<const float4*>(z + e)
-                 : make_float4(-FLT_MAX, -FLT_MAX, -FLT_MAX, -FLT_MAX);
-  }
-  float m = -FLT_MAX;
+  for (int k = 0; k < 4; ++k)
+    load_block<256>(z, b0 + 4 * k < n_blk ? V : 0, b0 + 4 * k, lane, v[k]);
 #pragma unroll
-  for (int q = 0; q < 16; ++q)
-    m = fmaxf(m, fmaxf(fmaxf(v[q].x, v[q].y), fmaxf(v[q].z, v[q].w)) * inv_t);
-  float sum = 0.f;
-  if (m > -FLT_MAX) {
+  for (int k = 0; k < 4; ++k) {
+    const int b = b0 + 4 * k;
+    if (b >= n_blk) break;
+    float m = -FLT_MAX;
 #pragma unroll
-    for (int q = 0; q < 16; ++q) {
-      const int e = base + 4 * (threadIdx.x + kThreads * q);
-      if (e < V)
-        sum += __expf(v[q].x * inv_t - m) + __expf(v[q].y * inv_t - m) +
-               __expf(v[q].z * inv_t - m) + __expf(v[q].w * inv_t - m);
+    for (int q = 0; q < 4; ++q)
+      m = fmaxf(m, fmaxf(fmaxf(v[k][q].x, v[k][q].y), fmaxf(v[k][q].z, v[k][q].w)));
+    m = wave_max(m);
+    const float ref = m * inv_t;
+    double sum = 0.0;
+    if (m > -FLT_MAX) {
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+        sum += ((double)__expf(v[k][q].x * inv_t - ref) +
+                (double)__expf(v[k][q].y * inv_t - ref)) +
+               ((double)__expf(v[k][q].z * inv_t - ref) +
+                (double)__expf(v[k][q].w * inv_t - ref));
     }
-  }
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1)
-    stat_merge(m, sum, __shfl_xor(m, o, SB_WAVE), __shfl_xor(sum, o, SB_WAVE));
-  __shared__ float wm[kThreads / 64], ws[kThreads / 64];
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  if (lane == 0) {
-    wm[w] = m;
-    ws[w] = sum;
-  }
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    for (int i = 1; i < kThreads / 64; ++i) stat_merge(m, sum, wm[i], ws[i]);
-    stats[((size_t)s * budget + n) * n_tiles + j] = make_float2(m, sum);
+    sum = wave_sum_d(sum);
+    if (lane == 0)
+      stats[((size_t)s * budget + n) * n_blk + b] = SampleStat{sum, ref, 0.f};
   }
 }
 
-__global__ __launch_bounds__(kThreads) void accept_sample_kernel(
-    TreeDims td, sb_tree t, const float* __restrict__ logits, int V,
-    float inv_t, const float2* __restrict__ stats, int n_tiles,
-    const float* __restrict__ u_acc, const float* __restrict__ u_bonus,
-    sb_accept_out out) {
-  __shared__ int par[512], tok[512];
+// A node's blocks, kLaneBlocks consecutive ones a lane, and its log-sum-exp.
+__device__ __forceinline__ void load_stats(const SampleStat* __restrict__ row,
+                                           int n_blk, int lane,
+                                           float (&bm)[kLaneBlocks],
+                                           double (&bs)[kLaneBlocks]) {
+#pragma unroll
+  for (int k = 0; k < kLaneBlocks; ++k) {
+    const int b = kLaneBlocks * lane + k;
+    SampleStat e{0.0, -FLT_MAX, 0.f};
+    if (b < n_blk) e = row[b];
+    bm[k] = e.m;
+    bs[k] = e.s;
+  }
+}
+__device__ __forceinline__ float merge_stats(const float (&bm)[kLaneBlocks],
+                                             const double (&bs)[kLaneBlocks]) {
+  float m = bm[0];
+#pragma unroll
+  for (int k = 1; k < kLaneBlocks; ++k) m = fmaxf(m, bm[k]);
+  m = wave_max(m);
+  float sum = 0.f;
+#pragma unroll
+  for (int k = 0; k < kLaneBlocks; ++k)
+    if (bs[k] > 0.0) sum += (float)bs[k] * __expf(bm[k] - m);
+  return m + logf(wave_sum(sum));
+}
+
+// Nodes of a sequence's tree in LDS.
+struct SampleTree {
+  int par[512], tok[512];
+  float ua[512];
+};
+
+// The walk (one wave of the workgroup; the tests are lane 0's).
+__device__ __forceinline__ void sample_walk(
+    const TreeDims& td, const sb_tree& t, const SampleTree& tr, int s,
+    const float* __restrict__ logits, int V, float inv_t,
+    const SampleStat* __restrict__ stats, int n_blk, const sb_accept_out& out,
+    SampleWalk& wk) {
   __shared__ int kid[kMaxKids];
-  __shared__ float kp[kMaxKids], ku[kMaxKids];
-  __shared__ int rej[kMaxKids];
-  __shared__ int sh_cur, sh_nrej, sh_bonus;
-  __shared__ float sh_lse;
-  // a tile of probabilities, padded so that thread t's 64 tokens start at
-  // 65 t (conflict-free reads), then the (thread, tile) scan of group masses
-  __shared__ float tile[kThreads * 65];
-  __shared__ double scan[kThreads][kMaxTiles + 1];   // padded rows
-  __shared__ double wtot[kThreads / 64][kMaxTiles];
-  const int s = blockIdx.x;
-  const int tid = threadIdx.x, lane = tid & 63;
+  __shared__ float kp[kMaxKids];
+  __shared__ int sh_next, sh_nrej;
+  const int lane = threadIdx.x & 63;
   const size_t nb = (size_t)s * td.budget;
   const int nn = min(t.n_nodes[s], td.budget);
   const int off = row_offset(t.n_nodes, s, td.budget);
   const int path_cap = td.M * td.K;
-  for (int j = tid; j < nn; j += kThreads) {
-    par[j] = t.parent[nb + j];
-    tok[j] = t.token[nb + j];
-  }
-  __syncthreads();
-  if (tid < 64) {
-    // ---- the walk, wave 0 ----
-    int cur = 0, a = 0, nrej = 0;
-    float l = 0.f;
-    while (true) {
-      // log-sum-exp of the node's row from its tile statistics
-      {
-        float m = -FLT_MAX, sm = 0.f;
-        if (lane < n_tiles) {
-          const float2 st = stats[(nb + cur) * n_tiles + lane];
-          m = st.x;
-          sm = st.y;
-        }
-#pragma unroll
-        for (int o = 32; o > 0; o >>= 1)
-          stat_merge(m, sm, __shfl_xor(m, o, SB_WAVE),
-                     __shfl_xor(sm, o, SB_WAVE));
-        l = m + logf(sm);
-      }
-      // children of cur in node-id order (ballot compaction)
-      int nk = 0;
-      for (int j0 = 1; j0 < nn; j0 += 64) {
-        const int j = j0 + lane;
-        const bool f = j < nn && par[j] == cur;
-        const uint64_t mk = __ballot(f);
-        const int pos = nk + __popcll(mk & ((1ull << lane) - 1ull));
-        if (f && pos < kMaxKids) kid[pos] = j;
-        nk += __popcll(mk);
-      }
-      nk = min(nk, kMaxKids);
-      const size_t zrow = (size_t)(off + cur) * V;
-      if (lane < nk) {
-        const int c = kid[lane];
-        const int x = tok[c];
-        // a token outside the vocabulary has no target mass
-        kp[lane] = (x >= 0 && x < V) ? __expf(logits[zrow + x] * inv_t - l)
-                                     : 0.f;
-        ku[lane] = u_acc[nb + c];
-      }
-      // sequential tests (lane 0), result broadcast through LDS
-      if (lane == 0) {
-        int next = -1;
-        float mass = 1.f;
-        nrej = 0;
-        for (int i = 0; i < nk; ++i) {
-          const int x = tok[kid[i]];
-          bool seen = false;
-          for (int r = 0; r < nrej; ++r) seen |= rej[r] == x;
-          if (seen) continue;
-          if (ku[i] < kp[i] / mass) {
-            next = kid[i];
-            break;
-          }
-          rej[nrej++] = x;
-          mass -= kp[i];
-        }
-        sh_cur = next;
-        sh_nrej = nrej;
-      }
-      __builtin_amdgcn_wave_barrier();
-      const int next = sh_cur;
-      nrej = sh_nrej;
-      if (next < 0 || a >= path_cap) break;
-      if (lane == 0) out.path[(size_t)s * path_cap + a] = next;
-      cur = next;
-      ++a;
+  int cur = 0, a = 0, nk = 0;
+#pragma unroll 1
+  while (true) {
+    const float* z = logits + (size_t)(off + cur) * V;
+    float bm[kLaneBlocks];
+    double bs[kLaneBlocks];
+    load_stats(stats + (nb + cur) * n_blk, n_blk, lane, bm, bs);
+    // children of cur in node-id order (ballot compaction), their logits on
+    // the way while the statistics are merged
+    nk = 0;
+    for (int j0 = 1; j0 < nn; j0 += 64) {
+      const int j = j0 + lane;
+      const bool f = j < nn && tr.par[j] == cur;
+      const uint64_t mk = __ballot(f);
+      const int pos = nk + __popcll(mk & ((1ull << lane) - 1ull));
+      if (f && pos < kMaxKids) kid[pos] = j;
+      nk += __popcll(mk);
     }
+    nk = min(nk, kMaxKids);
+    wave_lds_sync();
+    float zk = -FLT_MAX;
+    if (lane < nk) {
+      const int x = tr.tok[kid[lane]];
+      // a token outside the vocabulary has no target mass
+      if (x >= 0 && x < V) zk = z[x];
+    }
+    // (a leaf's statistics may not be there yet: it has no tests)
+    if (nk == 0) {
+      if (lane == 0) sh_nrej = 0;
+      break;
+    }
+    const float l = merge_stats(bm, bs);
+    if (lane < nk) kp[lane] = zk > -FLT_MAX ? __expf(zk * inv_t - l) : 0.f;
+    wave_lds_sync();
+    // sequential tests (lane 0), result broadcast through LDS
     if (lane == 0) {
-      out.n_accepted[s] = a;
-      sh_cur = cur;
-      sh_nrej = nrej;
-      sh_lse = l;
-      sh_bonus = -1;
-    }
-  }
-  __syncthreads();
-  // ---- residual draw at the last node, whole workgroup ----
-  // (runtime loops: this code runs once per launch, so its size, not its
-  // trip counts, sets the instruction-fetch cost)
-  const int cur = sh_cur, nrej = sh_nrej;
-  const float l = sh_lse;
-  const float* z = logits + (size_t)(off + cur) * V;
-  const int w = tid >> 6;
-  // tile j's logits in registers while tile j - 1 is summed
-  float4 v[16];
-#pragma unroll
-  for (int q = 0; q < 16; ++q) {
-    const int e = 4 * (tid + kThreads * q);
-    v[q] = e < V ? *reinterpret_cast<const float4*>(z + e)
-                 : make_float4(-FLT_MAX, -FLT_MAX, -FLT_MAX, -FLT_MAX);
-  }
+      int next = -1, n_rej = 0;
+      float mass = 1.f;
 #pragma unroll 1
-  for (int j = 0; j < n_tiles; ++j) {
-    const int base = j * kTile;
-#pragma unroll
-    for (int q = 0; q < 16; ++q) {
-      const int e = 4 * (tid + kThreads * q);
-      float* d = tile + e + e / 64;
-      // -FLT_MAX (past the vocabulary) gives exp = 0
-      d[0] = __expf(v[q].x * inv_t - l);
-      d[1] = __expf(v[q].y * inv_t - l);
-      d[2] = __expf(v[q].z * inv_t - l);
-      d[3] = __expf(v[q].w * inv_t - l);
-    }
-    if (j + 1 < n_tiles) {
-#pragma unroll
-      for (int q = 0; q < 16; ++q) {
-        const int e = base + kTile + 4 * (tid + kThreads * q);
-        v[q] = e < V ? *reinterpret_cast<const float4*>(z + e)
-                     : make_float4(-FLT_MAX, -FLT_MAX, -FLT_MAX, -FLT_MAX);
+      for (int i = 0; i < nk; ++i) {
+        const int x = tr.tok[kid[i]];
+        bool seen = false;
+        for (int r = 0; r < n_rej; ++r) seen |= wk.rej[r] == x;
+        if (seen) continue;
+        if (tr.ua[kid[i]] < kp[i] / mass) {
+          next = kid[i];
+          break;
+        }
+        wk.rej[n_rej++] = x;
+        mass -= kp[i];
       }
+      sh_next = next;
+      sh_nrej = n_rej;
     }
-    __syncthreads();
-    // rejected tokens leave the residual
-    if (tid < nrej) {
-      const int x = rej[tid] - base;
-      if (x >= 0 && x < kTile) tile[x + x / 64] = 0.f;
-    }
-    __syncthreads();
+    wave_lds_sync();
+    const int next = sh_next;
+    if (next < 0 || a >= path_cap) break;
+    if (lane == 0) out.path[(size_t)s * path_cap + a] = next;
+    cur = next;
+    ++a;
+  }
+  if (lane == 0) {
+    out.n_accepted[s] = a;
+    wk.cur = cur;
+    wk.leaf = nk == 0;
+    wk.nrej = sh_nrej;
+  }
+}
+
+// The residual draw at the node that the walk ended at (one wave); the bonus
+// token, in every lane.
+__device__ __forceinline__ int sample_draw(
+    const TreeDims& td, const sb_tree& t, int s, const float* __restrict__ logits,
+    int V, float inv_t, const SampleStat* __restrict__ stats, int n_blk,
+    const float* __restrict__ u_bonus, int cur, int nrej, const int* rej) {
+  const int lane = threadIdx.x & 63;
+  const size_t nb = (size_t)s * td.budget;
+  const float* z =
+      logits + (size_t)(row_offset(t.n_nodes, s, td.budget) + cur) * V;
+  float bm[kLaneBlocks];
+  double bs[kLaneBlocks];
+  load_stats(stats + (nb + cur) * n_blk, n_blk, lane, bm, bs);
+  const float l = merge_stats(bm, bs);
+  // block masses relative to l; those that hold a rejected token again,
+  // without the rejected ones
+#pragma unroll
+  for (int k = 0; k < kLaneBlocks; ++k)
+    bs[k] = bs[k] > 0.0 ? bs[k] * (double)__expf(bm[k] - l) : 0.0;
+#pragma unroll 1
+  for (int r = 0; r < nrej; ++r) {
+    const int b = rej[r] / kSampleBlock;
+    if (rej[r] < 0 || b >= n_blk) continue;
+    float4 v[4];
+    load_block<4>(z, V, b, lane, v);
+    float p[16];
+    block_probs(v, inv_t, l, kSampleBlock * b + 16 * lane, rej, nrej, p);
     double g = 0.0;
-#pragma unroll 8
-    for (int i = 0; i < 64; ++i) g += (double)tile[65 * tid + i];
-    // inclusive scan over the wave's threads
-    double incl = g;
 #pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-      const double t = __shfl_up(incl, o, SB_WAVE);
-      if (lane >= o) incl += t;
+    for (int i = 0; i < 16; ++i) g += (double)p[i];
+    g = wave_sum_d(g);
+#pragma unroll
+    for (int k = 0; k < kLaneBlocks; ++k)
+      if (kLaneBlocks * lane + k == b) bs[k] = g;
+  }
+  double incl = 0.0;
+#pragma unroll
+  for (int k = 0; k < kLaneBlocks; ++k) incl += bs[k];
+  const double mine = incl;
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) {
+    const double x = __shfl_up(incl, o, SB_WAVE);
+    if (lane >= o) incl += x;
+  }
+  const double total = __shfl(incl, 63, SB_WAVE);
+  const double target = (double)u_bonus[nb + cur] * total;
+  // the first block whose cumulative mass passes the target, and the mass
+  // before it; none (rounding): the last block with mass
+  int first = kMaxBlocks, last = -1;
+  double before = 0.0, lo = incl - mine;
+#pragma unroll
+  for (int k = 0; k < kLaneBlocks; ++k) {
+    const double hi = lo + bs[k];
+    if (bs[k] > 0.0) {
+      last = kLaneBlocks * lane + k;
+      if (first == kMaxBlocks && hi > target) {
+        first = kLaneBlocks * lane + k;
+        before = lo;
+      }
     }
-    scan[tid][j] = incl;
-    if (lane == 63) wtot[w][j] = incl;
+    lo = hi;
+  }
+  const int b_first = wave_min_i(first);
+  const int b_last = -wave_min_i(-last);
+  const bool past = b_first == kMaxBlocks;
+  const int b = past ? b_last : b_first;
+  if (b < 0) return 0;   // no mass at all
+  before = __shfl(before, b / kLaneBlocks, SB_WAVE);
+  // the token: lane i takes sixteen consecutive ones
+  const int x0 = kSampleBlock * b + 16 * lane;
+  float4 v[4];
+  load_block<4>(z, V, b, lane, v);
+  float p[16];
+  block_probs(v, inv_t, l, x0, rej, nrej, p);
+  double sum16 = 0.0;
+#pragma unroll
+  for (int i = 0; i < 16; ++i) sum16 += (double)p[i];
+  double in16 = sum16;
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) {
+    const double x = __shfl_up(in16, o, SB_WAVE);
+    if (lane >= o) in16 += x;
+  }
+  double acc = before + (in16 - sum16);
+  int pick = 0x7FFFFFFF, pos = -1;
+#pragma unroll
+  for (int i = 0; i < 16; ++i) {
+    if (p[i] > 0.f) pos = x0 + i;
+    acc += (double)p[i];
+    if (p[i] > 0.f && acc > target && pick == 0x7FFFFFFF) pick = x0 + i;
+  }
+  // (rounding can leave the running sum short of the block's end: the
+  // block's last token with mass is then the draw)
+  const int t_first = wave_min_i(pick);
+  const int t_last = -wave_min_i(-pos);
+  return !past && t_first != 0x7FFFFFFF ? t_first : max(t_last, 0);
+}
+
+// One workgroup per sequence: wave 0 walks (WALK) and draws (DRAW), then all
+// four waves compute the verifier-derived signal when it is asked for.  With
+// the two phases in separate launches, walk[s] carries the state between.
+template <typename T, bool WALK, bool DRAW>
+__global__ __launch_bounds__(256) void accept_sample_kernel(
+    TreeDims td, sb_tree t, const float* __restrict__ logits, int V,
+    float inv_t, const SampleStat* __restrict__ stats, int n_blk,
+    const float* __restrict__ u_acc, const float* __restrict__ u_bonus,
+    sb_accept_out out, SampleWalk* __restrict__ walk, SignalArgs g) {
+  __shared__ SampleWalk wk;
+  __shared__ int sh_bonus;
+  const int s = blockIdx.x, tid = threadIdx.x;
+  __shared__ SampleTree tr;
+  if constexpr (WALK) {
+    const size_t nb = (size_t)s * td.budget;
+    for (int j = tid; j < min(t.n_nodes[s], td.budget); j += 256) {
+      tr.par[j] = t.parent[nb + j];
+      tr.tok[j] = t.token[nb + j];
+      tr.ua[j] = u_acc[nb + j];
+    }
     __syncthreads();
   }
-  double total = 0.0;
-#pragma unroll 1
-  for (int j = 0; j < n_tiles; ++j)
-    total += (wtot[0][j] + wtot[1][j]) + (wtot[2][j] + wtot[3][j]);
-  const double target = (double)u_bonus[nb + cur] * total;
-  double toff = 0.0;
-#pragma unroll 1
-  for (int j = 0; j < n_tiles; ++j) {
-    double bw = toff;
-    for (int i = 0; i < w; ++i) bw += wtot[i][j];
-    const double lo = bw + (lane > 0 ? scan[tid - 1][j] : 0.0);
-    const double hi = bw + scan[tid][j];
-    toff += (wtot[0][j] + wtot[1][j]) + (wtot[2][j] + wtot[3][j]);
-    if (hi > lo && lo <= target && target < hi) {
-      // the group's residual probabilities, all loads in flight at once,
-      // into this thread's own (no longer shared) slice of the tile buffer
-      const int x0 = j * kTile + 64 * tid;
-      float* my = tile + 65 * tid;
-#pragma unroll
-      for (int q = 0; q < 16; ++q) {
-        const int x = x0 + 4 * q;
-        const float4 u = x < V ? *reinterpret_cast<const float4*>(z + x)
-                               : make_float4(-FLT_MAX, -FLT_MAX, -FLT_MAX,
-                                             -FLT_MAX);
-        my[4 * q] = __expf(u.x * inv_t - l);
-        my[4 * q + 1] = __expf(u.y * inv_t - l);
-        my[4 * q + 2] = __expf(u.z * inv_t - l);
-        my[4 * q + 3] = __expf(u.w * inv_t - l);
+  if (tid < 64) {
+    if constexpr (WALK) {
+      sample_walk(td, t, tr, s, logits, V, inv_t, stats, n_blk, out, wk);
+    } else {
+      wk.rej[tid] = walk[s].rej[tid];
+      if (tid == 0) {
+        wk.cur = walk[s].cur;
+        wk.nrej = walk[s].nrej;
       }
-#pragma unroll 1
-      for (int i = 0; i < nrej; ++i) {
-        const int x = rej[i] - x0;
-        if (x >= 0 && x < 64) my[x] = 0.f;
+    }
+    wave_lds_sync();
+    if constexpr (DRAW) {
+      const int b = sample_draw(td, t, s, logits, V, inv_t, stats, n_blk,
+                                u_bonus, wk.cur, wk.nrej, wk.rej);
+      if (tid == 0) {
+        out.bonus[s] = b;
+        sh_bonus = b;
       }
-      double acc = lo;
-      int pick = -1, last = -1;
-#pragma unroll 1
-      for (int i = 0; i < 64 && pick < 0; ++i) {
-        const float p = my[i];
-        if (p > 0.f) last = x0 + i;
-        acc += (double)p;
-        if (acc > target) pick = x0 + i;
+    } else {
+      walk[s].rej[tid] = tid < wk.nrej ? wk.rej[tid] : 0;
+      if (tid == 0) {
+        walk[s].cur = wk.cur;
+        walk[s].leaf = wk.leaf;
+        walk[s].nrej = wk.nrej;
       }
-      // rounding can leave the group's running sum short of its scanned
-      // end; the group's last positive token is then the draw
-      atomicMax(&sh_bonus, pick >= 0 ? pick : last);
     }
   }
-  __syncthreads();
-  if (tid == 0) {
-    int b = sh_bonus;
-    if (b < 0) {
-      // target at or past the total (rounding): the last token with mass
-      for (int x = V - 1; x >= 0 && b < 0; --x) {
-        bool r = false;
-        for (int i = 0; i < nrej; ++i) r |= rej[i] == x;
-        if (!r && __expf(z[x] * inv_t - l) > 0.f) b = x;
-      }
-      if (b < 0) b = 0;
-    }
-    out.bonus[s] = b;
+  if constexpr (DRAW) {
+    if (g.r == nullptr) return;
+    __syncthreads();
+    reject_signal_block<T>(td, t, s, wk.cur, sh_bonus, g);
   }
 }
 
-int sample_tiles(int V) { return (V + kTile - 1) / kTile; }
-int sample_max_vocab() { return kTile * kMaxTiles; }
+int sample_blocks(int V) { return (V + kSampleBlock - 1) / kSampleBlock; }
+int sample_max_vocab() { return kSampleBlock * kMaxBlocks; }
 
-void launch_node_stats(const float* logits, int V, float inv_t,
-                       const int* n_nodes, int n_seqs, int budget,
-                       float2* stats, hipStream_t st) {
-  dim3 grid(sample_tiles(V), budget, n_seqs);
-  node_stats_kernel<<<grid, kThreads, 0, st>>>(logits, V, inv_t, n_nodes,
-                                               budget, sample_tiles(V), stats);
+size_t sample_scratch(int n_seqs, int budget, int n_blk) {
+  return (size_t)n_seqs * budget * n_blk +
+         (n_seqs * sizeof(SampleWalk) + sizeof(SampleStat) - 1) / sizeof(SampleStat);
 }
+
+namespace {
+
+template <typename T>
+void launch_sample(const TreeDims& td, const sb_tree& t, const float* logits,
+                   int V, float inv_t, SampleStat* stats, const float* u_acc,
+                   const float* u_bonus, const sb_accept_out& o,
+                   const SignalArgs& g, hipStream_t st) {
+  const int n_blk = sample_blocks(V);
+  const int tiles = (n_blk + kTileBlocks - 1) / kTileBlocks;
+  SampleWalk* walk =
+      reinterpret_cast<SampleWalk*>(stats + (size_t)td.S * td.budget * n_blk);
+  const dim3 all(tiles, td.budget, td.S);
+  // Most nodes of a tree are leaves, whose statistics matter only where the
+  // walk ends at one.  With many rows, the inner nodes' statistics alone, the
+  // walk, those of the last nodes that are leaves and the draw take less than
+  // a pass over all rows: 65 against 86 us for 16 trees of at most 64 nodes
+  // (38 on average), 8 us less for four of 96.  With few rows the two more
+  // launches cost more than the rows that are not read (one tree of 60, 31 MB
+  // of logits: 2 to 5 us more); the line lies between the two.
+  if ((size_t)td.S * td.budget * V * 4 < ((size_t)96 << 20)) {
+    node_stats_kernel<kAllNodes><<<all, kThreads, 0, st>>>(
+        logits, V, inv_t, t.n_nodes, t.parent, td.budget, n_blk, walk, stats);
+    accept_sample_kernel<T, true, true><<<td.S, 256, 0, st>>>(
+        td, t, logits, V, inv_t, stats, n_blk, u_acc, u_bonus, o, walk, g);
+    return;
+  }
+  node_stats_kernel<kInnerNodes><<<all, kThreads, 0, st>>>(
+      logits, V, inv_t, t.n_nodes, t.parent, td.budget, n_blk, walk, stats);
+  accept_sample_kernel<T, true, false><<<td.S, 256, 0, st>>>(
+      td, t, logits, V, inv_t, stats, n_blk, u_acc, u_bonus, o, walk, g);
+  node_stats_kernel<kLastLeaf><<<dim3(tiles, 1, td.S), kThreads, 0, st>>>(
+      logits, V, inv_t, t.n_nodes, t.parent, td.budget, n_blk, walk, stats);
+  accept_sample_kernel<T, false, true><<<td.S, 256, 0, st>>>(
+      td, t, logits, V, inv_t, stats, n_blk, u_acc, u_bonus, o, walk, g);
+}
+
+}  // namespace
 
 void launch_accept_sample(const TreeDims& td, const sb_tree& t,
                           const float* logits, int V, float inv_t,
-                          const float2* stats, const float* u_acc,
+                          SampleStat* stats, const float* u_acc,
                           const float* u_bonus, const sb_accept_out& o,
-                          hipStream_t st) {
-  accept_sample_kernel<<<td.S, kThreads, 0, st>>>(
-      td, t, logits, V, inv_t, stats, sample_tiles(V), u_acc, u_bonus, o);
+                          const SignalArgs& g, bool bf16, hipStream_t st) {
+  if (bf16)
+    launch_sample<bf16_t>(td, t, logits, V, inv_t, stats, u_acc, u_bonus, o, g,
+                          st);
+  else
+    launch_sample<float>(td, t, logits, V, inv_t, stats, u_acc, u_bonus, o, g,
+                         st);
 }
 
 }  // namespace sb

@@ -7,6 +7,7 @@
 #include "bounds.h"
 #include "common.h"
 #include "kernels.h"
+#include "signal.h"
 #include "specblock.h"
 
 namespace sb {
@@ -315,115 +316,147 @@ __global__ void plan_verify_kernel(TreeDims td, sb_tree t,
   }
 }
 
-// Greedy acceptance walk, one wave per sequence.
-__global__ __launch_bounds__(64) void accept_kernel(TreeDims td, sb_tree t,
-                                                    const int* __restrict__ argmax,
-                                                    sb_accept_out out) {
+// Greedy acceptance walk, one workgroup per sequence: the tree is staged in
+// LDS, wave 0 walks, and the whole workgroup computes the verifier-derived
+// signal when it is asked for (g.r).
+template <typename T>
+__global__ __launch_bounds__(256) void accept_kernel(TreeDims td, sb_tree t,
+                                                     const int* __restrict__ argmax,
+                                                     sb_accept_out out,
+                                                     SignalArgs g) {
+  __shared__ int par[512], tok[512], am[512];
+  __shared__ int sh_cur, sh_bonus;
   const int s = blockIdx.x;
-  const int lane = threadIdx.x;
+  const int lane = threadIdx.x & 63;
   const size_t nb = (size_t)s * td.budget;
   const int nn = min(t.n_nodes[s], td.budget);
   const int path_cap = td.M * td.K;
-  int cur = 0, a = 0;
-  while (a < path_cap) {
-    const int g = argmax[nb + cur];
-    int best = 0x7FFFFFFF;
-    for (int j = 1 + lane; j < nn; j += 64)
-      if (t.parent[nb + j] == cur && t.token[nb + j] == g) best = min(best, j);
-    best = wave_min_i(best);
-    if (best == 0x7FFFFFFF) break;
-    if (lane == 0) out.path[(size_t)s * path_cap + a] = best;
-    cur = best;
-    ++a;
+  // (node 0's argmax is read whatever n_nodes says)
+  for (int j = threadIdx.x; j < td.budget; j += 256) {
+    par[j] = t.parent[nb + j];
+    tok[j] = t.token[nb + j];
+    am[j] = argmax[nb + j];
   }
-  if (lane == 0) {
-    out.n_accepted[s] = a;
-    out.bonus[s] = argmax[nb + cur];
+  __syncthreads();
+  if (threadIdx.x < 64) {
+    int cur = 0, a = 0;
+    while (a < path_cap) {
+      const int gr = am[cur];
+      int best = 0x7FFFFFFF;
+      for (int j = 1 + lane; j < nn; j += 64)
+        if (par[j] == cur && tok[j] == gr) best = min(best, j);
+      best = wave_min_i(best);
+      if (best == 0x7FFFFFFF) break;
+      if (lane == 0) out.path[(size_t)s * path_cap + a] = best;
+      cur = best;
+      ++a;
+    }
+    if (lane == 0) {
+      out.n_accepted[s] = a;
+      out.bonus[s] = am[cur];
+      sh_cur = cur;
+      sh_bonus = am[cur];
+    }
   }
-}
-
-// The drafter row at position pos(cur) + 1 on a path through node cur: the
-// next row of cur's block when cur is a chain node short of K, else row 1 of
-// a block started at cur; -1 when the tree has none.
-__device__ int continuing_row(const TreeDims& td, const sb_tree& t, int s,
-                              int cur) {
-  const size_t nb = (size_t)s * td.budget;
-  const size_t rb = (size_t)s * td.row_cap;
-  const int nrows = t.n_rows[s];
-  if (cur == 0) return nrows > 0 ? 0 : -1;
-  const int r = t.row[nb + cur];
-  if (t.rank[nb + cur] == 1 && t.row_k[rb + r] < td.K && r + 1 < nrows)
-    return r + 1;
-  for (int j = 0; j < nrows; ++j)
-    if (t.row_start[rb + j] == cur && t.row_k[rb + j] == 1) return j;
-  return -1;
+  if (g.r == nullptr) return;
+  __syncthreads();
+  reject_signal_block<T>(td, t, s, sh_cur, sh_bonus, g);
 }
 
 // Commit planning: last accepted node, the drafter row continuing it (or a
-// catch-up row when the tree has none) and the catch-up call plan.
-__global__ void commit_plan_kernel(TreeDims td, sb_tree t, sb_accept_out acc,
-                                   const int* __restrict__ T, CommitInfo ci,
-                                   CallPlan fb, int* __restrict__ taps_idx,
-                                   int* __restrict__ n_aux) {
+// catch-up row when the tree has none) and the catch-up call plan.  One
+// workgroup: a wave per sequence, then lane s of wave 0 plans sequence s's
+// catch-up row (a serial walk over the sequences took 18 us for 16).
+__global__ __launch_bounds__(1024) void commit_plan_kernel(
+    TreeDims td, sb_tree t, sb_accept_out acc, const int* __restrict__ T,
+    CommitInfo ci, CallPlan fb, int* __restrict__ taps_idx,
+    int* __restrict__ n_aux) {
+  __shared__ int a_s[SB_MAX_SEQS], cur_s[SB_MAX_SEQS], cont_s[SB_MAX_SEQS];
+  __shared__ int T_s[SB_MAX_SEQS];
   const int path_cap = td.M * td.K;
-  for (int s = threadIdx.x; s < td.S; s += blockDim.x) {
-    const size_t nb = (size_t)s * td.budget;
-    const size_t rb = (size_t)s * td.row_cap;
+  const int lane = threadIdx.x & 63;
+  for (int s = threadIdx.x >> 6; s < td.S; s += 16) {
     const int a = acc.n_accepted[s];
     const int cur = a > 0 ? acc.path[(size_t)s * path_cap + a - 1] : 0;
+    const int Ts = T[s];
     const int cont = continuing_row(td, t, s, cur);
-    ci.T_old[s] = T[s];
-    ci.a[s] = a;
-    ci.cur[s] = cur;
-    ci.cont[s] = cont;
+    if (lane == 0) {
+      ci.T_old[s] = T_s[s] = Ts;
+      ci.a[s] = a_s[s] = a;
+      ci.cur[s] = cur_s[s] = cur;
+      ci.cont[s] = cont_s[s] = cont;
+    }
   }
   __syncthreads();
-  if (threadIdx.x == 0) {
-    int o = 0;
-    for (int s = 0; s < td.S; ++s) {
-      fb.seq_off[s] = o;
-      const int a = ci.a[s];
-      fb.prefix_len[s] = ci.T_old[s] + a;   // drafter entries 1..T+a
-      if (ci.cont[s] < 0) {
-        const int cur = ci.cur[s];
-        const size_t nb = (size_t)s * td.budget;
-        fb.seq[o] = s;
-        fb.slot[o] = 0;
-        fb.pos[o] = ci.T_old[s] + a + 1;
-        fb.token[o] = t.token[nb + cur];
-        fb.k[o] = 1;
-        fb.pred[o] = o;
-        fb.cond[o] = o;
-        fb.out_row[o] = -1;
-        fb.kv_dst[o] = ci.T_old[s] + a;
-        for (int w = 0; w < fb.vis_words; ++w)
-          fb.vis[(size_t)o * fb.vis_words + w] = (w == 0) ? 1u : 0u;
-        fb.seg_len[s] = 1;
-        taps_idx[o] = s * td.budget + max(t.parent[nb + cur], 0);
-        ++o;
-      } else {
-        fb.seg_len[s] = 0;
-      }
-    }
-    fb.seq_off[td.S] = o;
-    *fb.n = o;
-    *n_aux = o;
+  const int s = threadIdx.x;
+  if (s >= 64) return;
+  const bool mine = s < td.S;
+  const uint64_t need = __ballot(mine && cont_s[s] < 0);
+  if (!mine) return;
+  const int o = __popcll(need & ((1ull << s) - 1ull));
+  fb.seq_off[s] = o;
+  fb.prefix_len[s] = T_s[s] + a_s[s];   // drafter entries 1..T+a
+  fb.seg_len[s] = cont_s[s] < 0 ? 1 : 0;
+  if (cont_s[s] < 0) {
+    const size_t nidx = (size_t)s * td.budget + cur_s[s];
+    fb.seq[o] = s;
+    fb.slot[o] = 0;
+    fb.pos[o] = T_s[s] + a_s[s] + 1;
+    fb.token[o] = t.token[nidx];
+    fb.k[o] = 1;
+    fb.pred[o] = o;
+    fb.cond[o] = o;
+    fb.out_row[o] = -1;
+    fb.kv_dst[o] = T_s[s] + a_s[s];
+    for (int w = 0; w < fb.vis_words; ++w)
+      fb.vis[(size_t)o * fb.vis_words + w] = (w == 0) ? 1u : 0u;
+    taps_idx[o] = s * td.budget + max(t.parent[nidx], 0);
+  }
+  if (s == 0) {
+    const int n = __popcll(need);
+    fb.seq_off[td.S] = n;
+    *fb.n = n;
+    *n_aux = n;
   }
 }
 
 // Copy committed K/V entries.  Target: the root and accepted nodes (verify
 // scratch slot = node id) to entries T .. T+a.  Drafter: the rows that
 // proposed the accepted nodes to entries T .. T+a-1 (positions T+1 ..
-// T+a), and the continuing row, if any, to entry T+a.
+// T+a), and the continuing row, if any, to entry T+a.  Grid (sequence, entry,
+// (layer, KV head)): the target's layers, then the drafter's, four heads per
+// workgroup, then one slice that sets the new sequence state.
 template <typename T>
-__global__ void commit_copy_kernel(TreeDims td, sb_tree t, sb_accept_out acc,
-                                   CommitInfo ci, int drafter, KVPools kv,
-                                   int pool_seqs, int Hkv, int hd) {
+__global__ __launch_bounds__(512) void commit_apply_kernel(
+    TreeDims td, sb_tree t, sb_accept_out acc, CommitInfo ci, KVPools tkv,
+    int tl, KVPools dkv, int dl, int pool_seqs, int Hkv, int hd, sb_seqs sq,
+    const float* __restrict__ taps) {
   const int s = blockIdx.x;
   const int j = blockIdx.y;               // 0 .. M K
-  const int l = blockIdx.z / Hkv, kh = blockIdx.z % Hkv;
   const int a = ci.a[s];
   const int T0 = ci.T_old[s];
+  const int z = 4 * blockIdx.z + (threadIdx.x >> 7);
+  if (blockIdx.z == gridDim.z - 1) {
+    if (j != 0) return;
+    // cond_taps = taps of the last accepted node: 3 d floats (d % 32 == 0);
+    // the destination cannot alias the taps
+    const float4* __restrict__ src = reinterpret_cast<const float4*>(
+        taps + ((size_t)s * td.budget + ci.cur[s]) * 3 * td.d);
+    float4* __restrict__ dst =
+        reinterpret_cast<float4*>(sq.cond_taps + (size_t)s * 3 * td.d);
+#pragma unroll 4
+    for (int e = threadIdx.x; e < 3 * td.d / 4; e += 512) dst[e] = src[e];
+    if (threadIdx.x == 0) {
+      sq.T[s] = T0 + a + 1;
+      sq.root[s] = acc.bonus[s];
+    }
+    return;
+  }
+  if (z >= (tl + dl) * Hkv) return;
+  const bool drafter = z >= tl * Hkv;
+  const KVPools& kv = drafter ? dkv : tkv;
+  const int lz = z - (drafter ? tl * Hkv : 0);
+  const int l = lz / Hkv, kh = lz % Hkv;
   const int path_cap = td.M * td.K;
   int src_slot, dst;
   if (!drafter) {
@@ -457,56 +490,9 @@ __global__ void commit_copy_kernel(TreeDims td, sb_tree t, sb_accept_out acc,
   const T* sv = static_cast<const T*>(kv.seg_v) + src_page * 16 * hd;
   T* dk = static_cast<T*>(kv.k) + dst_page * 16 * hd;
   T* dv = static_cast<T*>(kv.v) + dst_page * 16 * hd;
-  for (int e = threadIdx.x; e < hd; e += blockDim.x) {
+  for (int e = threadIdx.x & 127; e < hd; e += 128) {
     dk[sl * hd + e] = sk[ss * hd + e];
     dv[e * 16 + sl] = sv[e * 16 + ss];
-  }
-}
-
-// Rows of a plan whose kv_dst >= 0: segment slot -> cache entry kv_dst.
-template <typename T>
-__global__ void seg_to_cache_kernel(CallPlan p, KVPools kv, int S, int Hkv,
-                                    int hd) {
-  const int i = blockIdx.x;
-  if (i >= *p.n) return;
-  const int dst = p.kv_dst[i];
-  if (dst < 0) return;
-  const int l = blockIdx.y / Hkv, kh = blockIdx.y % Hkv;
-  const int s = p.seq[i], slot = p.slot[i];
-  const int page_i = dst >> 4;
-  if (page_i >= kv.max_pages) return;
-  const int page = checked_index(kv.page_table[(size_t)s * kv.max_pages + page_i],
-                                 kv.n_pages, kv.err, kDevPage);
-  const int sl = dst & 15;
-  const int sp = slot >> 4, ss = slot & 15;
-  if (sp >= kv.seg_pages) return;
-  const size_t src_page = (((size_t)l * S + s) * kv.seg_pages + sp) * Hkv + kh;
-  const size_t dst_page = ((size_t)l * kv.n_pages + page) * Hkv + kh;
-  const T* sk = static_cast<const T*>(kv.seg_k) + src_page * 16 * hd;
-  const T* sv = static_cast<const T*>(kv.seg_v) + src_page * 16 * hd;
-  T* dk = static_cast<T*>(kv.k) + dst_page * 16 * hd;
-  T* dv = static_cast<T*>(kv.v) + dst_page * 16 * hd;
-  for (int e = threadIdx.x; e < hd; e += blockDim.x) {
-    dk[sl * hd + e] = sk[ss * hd + e];
-    dv[e * 16 + sl] = sv[e * 16 + ss];
-  }
-}
-
-__global__ void commit_state_kernel(TreeDims td, sb_seqs sq, sb_accept_out acc,
-                                    CommitInfo ci, const float* __restrict__ taps) {
-  const int s = blockIdx.x;
-  const int cur = ci.cur[s];
-  // 3 d floats (d % 32 == 0): float4 copy, every load issued before the
-  // stores (the destination cannot alias the taps)
-  const float4* __restrict__ src = reinterpret_cast<const float4*>(
-      taps + ((size_t)s * td.budget + cur) * 3 * td.d);
-  float4* __restrict__ dst =
-      reinterpret_cast<float4*>(sq.cond_taps + (size_t)s * 3 * td.d);
-  const int n4 = 3 * td.d / 4;
-  for (int e = threadIdx.x; e < n4; e += blockDim.x) dst[e] = src[e];
-  if (threadIdx.x == 0) {
-    sq.T[s] = ci.T_old[s] + ci.a[s] + 1;
-    sq.root[s] = acc.bonus[s];
   }
 }
 
@@ -609,113 +595,28 @@ void launch_plan_verify(const TreeDims& td, const sb_tree& t, const int* T,
                         const CallPlan& p, hipStream_t st) {
   plan_verify_kernel<<<1, 256, 0, st>>>(td, t, T, p);
 }
-// Verifier-derived update signal (Sec. 3.4, Eq. 8): at the rejected position
-// (the one after the last accepted node, where the bonus token stands), the
-// drafter's probability r of the target's token, from the row that predicted
-// that position: r = exp(z[bonus] - lse) with z[bonus] = W_lm[bonus] .
-// norm(h^(L)) recomputed from the row's cached h^(L) (the final RMSNorm and
-// the LM-head operand rounding of the drafter forward), lse the row's
-// log-sum-exp.  -1 when no drafter row predicts that position; 0 when the
-// bonus token is outside a reduced drafter vocabulary.
-template <typename T>
-__global__ __launch_bounds__(256) void reject_signal_kernel(
-    TreeDims td, sb_tree t, sb_accept_out acc, const float* __restrict__ row_lse,
-    const T* __restrict__ lm_head, const float* __restrict__ gain, float eps,
-    const int* __restrict__ d2t, int Vd, float* __restrict__ r_out) {
-  __shared__ float red[4];
-  __shared__ int sh_id;
-  const int s = blockIdx.x, tid = threadIdx.x;
-  const int path_cap = td.M * td.K;
-  const int a = acc.n_accepted[s];
-  const int cur = a > 0 ? acc.path[(size_t)s * path_cap + a - 1] : 0;
-  const int cont = continuing_row(td, t, s, cur);
-  if (cont < 0) {
-    if (tid == 0) r_out[s] = -1.f;
-    return;
-  }
-  const int bonus = acc.bonus[s];
-  if (tid == 0) {
-    int id = -1;
-    if (d2t == nullptr) {
-      id = (bonus >= 0 && bonus < Vd) ? bonus : -1;
-    } else {   // d2t is strictly increasing: binary search
-      int lo = 0, hi = Vd - 1;
-      while (lo <= hi) {
-        const int mid = (lo + hi) >> 1;
-        const int v = d2t[mid];
-        if (v == bonus) {
-          id = mid;
-          break;
-        }
-        if (v < bonus) lo = mid + 1;
-        else hi = mid - 1;
-      }
-    }
-    sh_id = id;
-  }
-  __syncthreads();
-  const int id = sh_id;
-  if (id < 0) {
-    if (tid == 0) r_out[s] = 0.f;
-    return;
-  }
-  const int d = td.d;
-  const size_t o = (size_t)s * td.row_cap + cont;
-  const float* h = t.h_last + o * d;
-  const int lane = tid & 63, w = tid >> 6;
-  float ss = 0.f;
-  for (int k = tid; k < d; k += 256) ss += h[k] * h[k];
-  ss = wave_sum(ss);
-  if (lane == 0) red[w] = ss;
-  __syncthreads();
-  const float rs = 1.0f / sqrtf((red[0] + red[1] + red[2] + red[3]) / (float)d + eps);
-  __syncthreads();
-  // eight consecutive columns per step: one 16-byte run of the packed
-  // (or row-major) LM-head row, all loads independent
-  float z = 0.f;
-  for (int k0 = 8 * tid; k0 < d; k0 += 8 * 256) {
-    size_t wi;
-    if constexpr (sizeof(T) == 2) {
-      // fragment-packed LM head (32-row x 64-column blocks)
-      const int c = k0 & 63;
-      const int l = (id & 31) + 32 * (c >> 5);
-      wi = ((((size_t)(k0 >> 6) * (Vd >> 5) + (id >> 5)) * 4 + ((c & 31) >> 3)) *
-            512) + (size_t)l * 8;
-    } else {
-      wi = (size_t)id * d + k0;
-    }
-#pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      const float x = Elem<T>::to_f32(
-          Elem<T>::from_f32(h[k0 + e] * rs * gain[k0 + e]));
-      z += Elem<T>::to_f32(lm_head[wi + e]) * x;
-    }
-  }
-  z = wave_sum(z);
-  if (lane == 0) red[w] = z;
-  __syncthreads();
-  if (tid == 0)
-    r_out[s] = __expf((red[0] + red[1] + red[2] + red[3]) - row_lse[o]);
-}
-
 void launch_accept(const TreeDims& td, const sb_tree& t, const int* argmax,
-                   const sb_accept_out& o, hipStream_t st) {
-  accept_kernel<<<td.S, 64, 0, st>>>(td, t, argmax, o);
+                   const sb_accept_out& o, const SignalArgs& g, bool bf16,
+                   hipStream_t st) {
+  if (bf16)
+    accept_kernel<bf16_t><<<td.S, 256, 0, st>>>(td, t, argmax, o, g);
+  else
+    accept_kernel<float><<<td.S, 256, 0, st>>>(td, t, argmax, o, g);
 }
 // Adaptation buffer push (Sec. 3.4): each sequence's rejected position
 // (the one after its last accepted node) whose drafter row exists appends
 // (that row's cached h^(L), the bonus token) to the buffer, in sequence
 // order, while room is left.  One workgroup.
-__global__ __launch_bounds__(256) void adapt_push_kernel(
+__global__ __launch_bounds__(1024) void adapt_push_kernel(
     TreeDims td, sb_tree t, sb_accept_out acc, float* __restrict__ buf_h,
     int* __restrict__ buf_y, int* __restrict__ count, int cap) {
   __shared__ int slot[SB_MAX_SEQS], src[SB_MAX_SEQS];
   const int path_cap = td.M * td.K;
-  if (threadIdx.x < td.S) {
-    const int s = threadIdx.x;
+  for (int s = threadIdx.x >> 6; s < td.S; s += 16) {
     const int a = acc.n_accepted[s];
     const int cur = a > 0 ? acc.path[(size_t)s * path_cap + a - 1] : 0;
-    src[s] = continuing_row(td, t, s, cur);
+    const int r = continuing_row(td, t, s, cur);
+    if ((threadIdx.x & 63) == 0) src[s] = r;
   }
   __syncthreads();
   if (threadIdx.x == 0) {
@@ -735,60 +636,31 @@ __global__ __launch_bounds__(256) void adapt_push_kernel(
     if (slot[s] < 0) continue;
     const float* hs = t.h_last + ((size_t)s * td.row_cap + src[s]) * d;
     float* hd = buf_h + (size_t)slot[s] * d;
-    for (int k = threadIdx.x; k < d; k += 256) hd[k] = hs[k];
+    for (int k = threadIdx.x; k < d; k += 1024) hd[k] = hs[k];
   }
 }
 
 void launch_adapt_push(const TreeDims& td, const sb_tree& t,
                        const sb_accept_out& acc, float* buf_h, int* buf_y,
                        int* count, int cap, hipStream_t st) {
-  adapt_push_kernel<<<1, 256, 0, st>>>(td, t, acc, buf_h, buf_y, count, cap);
+  adapt_push_kernel<<<1, 1024, 0, st>>>(td, t, acc, buf_h, buf_y, count, cap);
 }
 
-template <typename T>
-void launch_reject_signal(const TreeDims& td, const sb_tree& t,
-                          const sb_accept_out& acc, const float* row_lse,
-                          const T* lm_head, const float* gain, float eps,
-                          const int* d2t, int Vd, float* r_out,
-                          hipStream_t st) {
-  reject_signal_kernel<T><<<td.S, 256, 0, st>>>(td, t, acc, row_lse, lm_head,
-                                                gain, eps, d2t, Vd, r_out);
-}
-template void launch_reject_signal<float>(const TreeDims&, const sb_tree&,
-                                          const sb_accept_out&, const float*,
-                                          const float*, const float*, float,
-                                          const int*, int, float*,
-                                          hipStream_t);
-template void launch_reject_signal<bf16_t>(const TreeDims&, const sb_tree&,
-                                           const sb_accept_out&, const float*,
-                                           const bf16_t*, const float*, float,
-                                           const int*, int, float*,
-                                           hipStream_t);
 void launch_commit_plan(const TreeDims& td, const sb_tree& t,
                         const sb_accept_out& acc, const int* T,
                         const CommitInfo& ci, const CallPlan& fb,
                         int* taps_idx, int* n_aux, hipStream_t st) {
-  commit_plan_kernel<<<1, 64, 0, st>>>(td, t, acc, T, ci, fb, taps_idx, n_aux);
+  commit_plan_kernel<<<1, 1024, 0, st>>>(td, t, acc, T, ci, fb, taps_idx, n_aux);
 }
 template <typename T>
-void launch_commit_copy(const TreeDims& td, const sb_tree& t,
-                        const sb_accept_out& acc, const CommitInfo& ci,
-                        bool drafter, const KVPools& kv, int pool_seqs,
-                        int n_layers, int Hkv, int hd, hipStream_t st) {
-  dim3 grid(td.S, td.M * td.K + 1, n_layers * Hkv);
-  commit_copy_kernel<T><<<grid, 128, 0, st>>>(td, t, acc, ci, drafter ? 1 : 0,
-                                              kv, pool_seqs, Hkv, hd);
-}
-template <typename T>
-void launch_seg_to_cache(const CallPlan& p, const KVPools& kv, int S,
-                         int n_layers, int Hkv, int hd, hipStream_t st) {
-  dim3 grid(p.cap, n_layers * Hkv);
-  seg_to_cache_kernel<T><<<grid, 128, 0, st>>>(p, kv, S, Hkv, hd);
-}
-void launch_commit_state(const TreeDims& td, const sb_seqs& sq,
+void launch_commit_apply(const TreeDims& td, const sb_tree& t,
                          const sb_accept_out& acc, const CommitInfo& ci,
-                         const float* taps, hipStream_t st) {
-  commit_state_kernel<<<td.S, 1024, 0, st>>>(td, sq, acc, ci, taps);
+                         const KVPools& tkv, int tl, const KVPools& dkv,
+                         int dl, int pool_seqs, int Hkv, int hd,
+                         const sb_seqs& sq, const float* taps, hipStream_t st) {
+  dim3 grid(td.S, td.M * td.K + 1, ((tl + dl) * Hkv + 3) / 4 + 1);
+  commit_apply_kernel<T><<<grid, 512, 0, st>>>(td, t, acc, ci, tkv, tl, dkv,
+                                               dl, pool_seqs, Hkv, hd, sq, taps);
 }
 void launch_plan_prefill(const PrefillPass& pass, bool drafter,
                          const int* prompt, int ld, const CallPlan& p,
@@ -820,18 +692,12 @@ void launch_copy_int(int* dst, const int* src, hipStream_t st) {
   copy_int_kernel<<<1, 1, 0, st>>>(dst, src);
 }
 
-template void launch_commit_copy<float>(const TreeDims&, const sb_tree&,
-                                        const sb_accept_out&, const CommitInfo&,
-                                        bool, const KVPools&, int, int, int,
-                                        int, hipStream_t);
-template void launch_commit_copy<bf16_t>(const TreeDims&, const sb_tree&,
-                                         const sb_accept_out&,
-                                         const CommitInfo&, bool,
-                                         const KVPools&, int, int, int, int,
-                                         hipStream_t);
-template void launch_seg_to_cache<float>(const CallPlan&, const KVPools&, int,
-                                         int, int, int, hipStream_t);
-template void launch_seg_to_cache<bf16_t>(const CallPlan&, const KVPools&, int,
-                                          int, int, int, hipStream_t);
-
+#define SB_APPLY(T)                                                           \
+  template void launch_commit_apply<T>(                                       \
+      const TreeDims&, const sb_tree&, const sb_accept_out&,                  \
+      const CommitInfo&, const KVPools&, int, const KVPools&, int, int, int,  \
+      int, const sb_seqs&, const float*, hipStream_t);
+SB_APPLY(float)
+SB_APPLY(bf16_t)
+#undef SB_APPLY
 }  // namespace sb
