@@ -147,6 +147,7 @@ __global__ __launch_bounds__(64) void attach_kernel(
   __shared__ int br_s[kAttachRows];
   __shared__ int bk_s[kAttachRows];
   __shared__ float cand_s[kAttachRows];   // new node id - first_new
+  __shared__ uint32_t anc_s[SB_MAX_ANC_WORDS][64];   // a lane's chain node
   const int s = blockIdx.x;
   const int lane = threadIdx.x;
   const int K = td.K, budget = td.budget, bw = td.bw;
@@ -171,15 +172,11 @@ __global__ __launch_bounds__(64) void attach_kernel(
   bool alive = mine;
   int chain_depth = 0;
   float chain_cum = 0.f;
-  uint32_t chain_anc[SB_MAX_ANC_WORDS];
-#pragma unroll
-  for (int w = 0; w < SB_MAX_ANC_WORDS; ++w) chain_anc[w] = 0u;
   if (mine) {
     chain_depth = t.depth[nb + chain];
     chain_cum = t.cum_logp[nb + chain];
-#pragma unroll
-    for (int w = 0; w < SB_MAX_ANC_WORDS; ++w)
-      if (w < bw) chain_anc[w] = t.anc[(nb + chain) * bw + w];
+#pragma unroll 2
+    for (int w = 0; w < bw; ++w) anc_s[w][lane] = t.anc[(nb + chain) * bw + w];
   }
   int nn = t.n_nodes[s];
   const int first_new = nn;
@@ -196,6 +193,7 @@ __global__ __launch_bounds__(64) void attach_kernel(
       const float l0 = lse_s[j];
       const int bk = bk_s[j];
       const bool cand_row = bk == 1 || bk == 2;
+#pragma unroll 1
       for (int rank = 1; rank <= want; ++rank) {
         const int id = id0 + rank - 1;
         if (id >= budget) break;
@@ -209,19 +207,16 @@ __global__ __launch_bounds__(64) void attach_kernel(
         t.logp[nb + id] = lp;
         t.cum_logp[nb + id] = chain_cum + lp;
         if (rank >= 2 && cand_row) cand_s[id - first_new] = chain_cum + lp;
-#pragma unroll
-        for (int w = 0; w < SB_MAX_ANC_WORDS; ++w)
-          if (w < bw)
-            t.anc[(nb + id) * bw + w] =
-                chain_anc[w] | ((id >> 5) == w ? (1u << (id & 31)) : 0u);
+#pragma unroll 2
+        for (int w = 0; w < bw; ++w)
+          t.anc[(nb + id) * bw + w] =
+              anc_s[w][lane] | ((id >> 5) == w ? (1u << (id & 31)) : 0u);
       }
       if (want >= 1 && id0 < budget) {
         chain = id0;
         chain_depth += 1;
         chain_cum += lg_s[j * SB_TOPK_K] - l0;
-#pragma unroll
-        for (int w = 0; w < SB_MAX_ANC_WORDS; ++w)
-          if ((id0 >> 5) == w) chain_anc[w] |= 1u << (id0 & 31);
+        anc_s[id0 >> 5][lane] |= 1u << (id0 & 31);
       } else {
         alive = false;
       }
@@ -242,31 +237,37 @@ __global__ __launch_bounds__(64) void attach_kernel(
   const int e_excl = wave_excl_scan_small<1>(is_end, n_ends);
   if (is_end && e_excl < td.B_max) out[e_excl] = chain;
   int taken = min(n_ends, td.B_max);
-  // candidate mask per lane: node first_new + lane + 64 q
-  uint32_t cand = 0u;
+  // candidates of a lane: nodes first_new + lane + 64 q (values in registers;
+  // most blocks add at most 64 nodes, and then one round of q is all)
+  const int nq = (nn - first_new + 63) >> 6;
+  float cand[8];
+#pragma unroll
   for (int q = 0; q < 8; ++q) {
-    const int id = first_new + lane + 64 * q;
-    if (id < nn && cand_s[id - first_new] > -FLT_MAX) cand |= 1u << q;
+    const int j = lane + 64 * q;
+    cand[q] = q < nq && first_new + j < nn ? cand_s[j] : -FLT_MAX;
   }
+#pragma unroll 1
   while (taken < td.B_max) {
-    float bv = -FLT_MAX;
-    int bi = 0x7FFFFFFF;
-    for (int q = 0; q < 8; ++q) {
-      if (cand & (1u << q)) {
-        const int id = first_new + lane + 64 * q;
-        const float v = cand_s[id - first_new];
-        if (better(v, id, bv, bi)) {
-          bv = v;
-          bi = id;
+    float v = cand[0];
+    int q0 = 0;
+    if (nq > 1) {
+#pragma unroll
+      for (int q = 1; q < 8; ++q)
+        if (cand[q] > v) {          // equal values: the lower id stays
+          v = cand[q];
+          q0 = q;
         }
-      }
     }
-    float v = bv;
-    int id = bi;
+    int id = v > -FLT_MAX ? first_new + lane + 64 * q0 : 0x7FFFFFFF;
     wave_best_pair(v, id);
     if (id == 0x7FFFFFFF) break;
     if (lane == 0) out[taken] = id;
-    if (((id - first_new) & 63) == lane) cand &= ~(1u << ((id - first_new) >> 6));
+    const int j = id - first_new;
+    if ((j & 63) == lane) {
+#pragma unroll
+      for (int q = 0; q < 8; ++q)
+        if (q == (j >> 6)) cand[q] = -FLT_MAX;
+    }
     ++taken;
   }
   if (lane == 0) t.n_starts[s] = taken;

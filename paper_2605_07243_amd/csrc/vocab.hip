@@ -98,18 +98,19 @@ __device__ __forceinline__ void wave_topk(float (&tv)[KT], int (&ti)[KT],
 // Candidate list of the threshold filter (values, ids) per workgroup.
 constexpr int kCandCap = 256;
 
-// Partial record of one (row, chunk).  The chunk is staged in LDS with
-// coalesced 16-byte loads; a thread owns elements v0 + tid, v0 + tid + 256,
-// ... .  Pass 1 takes each thread's maximum (and, for KT = 1, its first
-// arg-max); pass 2 sums exp(z - max) and exp(z - max) z against that maximum
-// and, for KT > 1, collects the candidates z >= T, where T is a lower bound
-// of the chunk's KT-th largest logit: in each wave, the KT-th largest
-// distinct value among the 64 thread maxima (KT of the wave's logits are at
-// least that large), the largest over the waves.  The candidates, usually a
-// dozen or two, are ordered by rank (value, then smaller id); a chunk with
-// more than kCandCap candidates (many equal logits) falls back to per-thread
-// sorted lists merged wave by wave.
-template <int KT>
+// Partial record of one (row, chunk).  A thread holds NV float4 of the chunk
+// in registers, float4 tid, tid + 256, ... (all loads in flight at once; a
+// chunk staged in LDS left three workgroups to a CU and took 123 us for 512
+// rows of 128256 logits, this form 56).  Pass 1 takes each thread's maximum
+// (and, for KT = 1, its first arg-max); pass 2 sums exp(z - max) and
+// exp(z - max) z against that maximum and, for KT > 1, collects the
+// candidates z >= T, where T is a lower bound of the chunk's KT-th largest
+// logit: in each wave, the KT-th largest distinct value among the 64 thread
+// maxima (KT of the wave's logits are at least that large), the largest over
+// the waves.  The candidates, usually a dozen or two, are ordered by rank
+// (value, then smaller id); a chunk with more than kCandCap candidates (many
+// equal logits) falls back to per-thread sorted lists merged wave by wave.
+template <int KT, int NV>
 __global__ __launch_bounds__(256) void vocab_partial_kernel(
     const float* __restrict__ logits, const int* __restrict__ n, int V,
     int chunk, float* __restrict__ part) {
@@ -117,8 +118,7 @@ __global__ __launch_bounds__(256) void vocab_partial_kernel(
   if (i >= *n) return;
   const int c = blockIdx.x;
   const int v0 = c * chunk, v1 = min(V, v0 + chunk);
-  const float* z = logits + (size_t)i * V;
-  extern __shared__ float zs[];
+  const float4* z = reinterpret_cast<const float4*>(logits + (size_t)i * V + v0);
   __shared__ float sm[4], ss[4], su[4], thr[4];
   __shared__ float cv[kCandCap], ov[4][KT];
   __shared__ int ci[kCandCap], oi[4][KT];
@@ -126,19 +126,41 @@ __global__ __launch_bounds__(256) void vocab_partial_kernel(
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   if (threadIdx.x == 0) n_cand = 0;
   const int nvec = v1 > v0 ? (v1 - v0) >> 2 : 0;
-#pragma unroll 8
-  for (int e = threadIdx.x; e < nvec; e += 256)
-    reinterpret_cast<float4*>(zs)[e] =
-        *reinterpret_cast<const float4*>(z + v0 + 4 * e);
-  __syncthreads();
+  float4 zv[NV];
+#pragma unroll
+  for (int q = 0; q < NV; ++q) {
+    const int e = threadIdx.x + 256 * q;
+    // past the chunk: below every logit, and no candidate (see the tests)
+    zv[q] = e < nvec ? z[e]
+                     : make_float4(-INFINITY, -INFINITY, -INFINITY, -INFINITY);
+  }
+  // the chunk's elements in order of their ids: f(value, id)
+  auto each = [&](auto f) {
+#pragma unroll
+    for (int q = 0; q < NV; ++q) {
+      const int e = threadIdx.x + 256 * q;
+      if (e < nvec) {
+        const int j = v0 + 4 * e;
+        f(zv[q].x, j);
+        f(zv[q].y, j + 1);
+        f(zv[q].z, j + 2);
+        f(zv[q].w, j + 3);
+      }
+    }
+  };
   float mx = -FLT_MAX;
   int mi = 0x7FFFFFFF;
-  for (int j = v0 + threadIdx.x; j < v1; j += 256) {
-    const float x = zs[j - v0];
-    if (x > mx) {
-      mx = x;
-      mi = j;
-    }
+  if constexpr (KT == 1) {
+    each([&](float x, int j) {
+      if (x > mx) {
+        mx = x;
+        mi = j;
+      }
+    });
+  } else {
+#pragma unroll
+    for (int q = 0; q < NV; ++q)
+      mx = fmaxf(mx, fmaxf(fmaxf(zv[q].x, zv[q].y), fmaxf(zv[q].z, zv[q].w)));
   }
   float tb = -FLT_MAX;
   if constexpr (KT > 1) {
@@ -155,8 +177,7 @@ __global__ __launch_bounds__(256) void vocab_partial_kernel(
     tb = fmaxf(fmaxf(fmaxf(thr[0], thr[1]), fmaxf(thr[2], thr[3])), -FLT_MAX);
   }
   float s = 0.f, u = 0.f;
-  for (int j = v0 + threadIdx.x; j < v1; j += 256) {
-    const float x = zs[j - v0];
+  each([&](float x, int j) {
     const float e = __expf(x - mx);
     s += e;
     u = fmaf(e, x, u);
@@ -169,7 +190,7 @@ __global__ __launch_bounds__(256) void vocab_partial_kernel(
         }
       }
     }
-  }
+  });
   const float m = mx;
   float M = m, S = s, U = u;
   wave_stats(M, S, U);
@@ -224,10 +245,9 @@ __global__ __launch_bounds__(256) void vocab_partial_kernel(
         tv[k] = -FLT_MAX;
         ti[k] = 0x7FFFFFFF;
       }
-      for (int j = v0 + threadIdx.x; j < v1; j += 256) {
-        const float x = zs[j - v0];
+      each([&](float x, int j) {
         if (x >= tb) topk_insert<KT>(tv, ti, x, j);
-      }
+      });
       float bv[KT];
       int bi[KT];
       wave_topk<KT>(tv, ti, bv, bi);
@@ -270,19 +290,22 @@ __global__ __launch_bounds__(256) void vocab_partial_kernel(
 int launch_vocab_partial(const float* logits, const int* n, int cap, int V,
                          int max_chunks, int topk, float* part,
                          hipStream_t st) {
-  // chunks of at most kVocabChunkMax logits (48 KiB LDS stage), about 2048
-  // workgroups when the row capacity allows, at most max_chunks (the record
-  // buffer, sized for at least ceil(V / kVocabChunkMax))
+  // chunks of at most kVocabChunkMax logits (twelve float4 a thread), about
+  // 2048 workgroups when the row capacity allows, at most max_chunks (the
+  // record buffer, sized for at least ceil(V / kVocabChunkMax))
   int n_chunks = std::max(1, std::min(max_chunks, (2048 + cap - 1) / cap));
   n_chunks = std::max(n_chunks, (V + kVocabChunkMax - 1) / kVocabChunkMax);
   const int chunk = (((V + n_chunks - 1) / n_chunks) + 3) & ~3;
   const dim3 grid(n_chunks, cap);
-  const size_t lds = (size_t)chunk * sizeof(float);
-  if (topk == 1)
-    vocab_partial_kernel<1><<<grid, 256, lds, st>>>(logits, n, V, chunk, part);
-  else
-    vocab_partial_kernel<SB_TOPK_K><<<grid, 256, lds, st>>>(logits, n, V, chunk,
-                                                            part);
+#define SB_VOCAB(NV_)                                                         \
+  if (chunk <= 1024 * NV_) {                                                  \
+    auto k = topk == 1 ? vocab_partial_kernel<1, NV_>                         \
+                       : vocab_partial_kernel<SB_TOPK_K, NV_>;                \
+    k<<<grid, 256, 0, st>>>(logits, n, V, chunk, part);                       \
+    return n_chunks;                                                          \
+  }
+  SB_VOCAB(3) SB_VOCAB(12)
+#undef SB_VOCAB
   return n_chunks;
 }
 
@@ -301,7 +324,20 @@ __device__ __forceinline__ void merge_row(const float* __restrict__ part,
     ti[k] = 0x7FFFFFFF;
   }
   float m = -FLT_MAX, s = 0.f, u = 0.f;
-  for (int c = lane; c < n_chunks; c += SB_WAVE) {
+  // (a record's values are sorted: a lane's first one is its list as it is)
+  if (lane < n_chunks) {
+    const float* o = part + (size_t)lane * (2 * KT + 3);
+#pragma unroll
+    for (int k = 0; k < KT; ++k) {
+      tv[k] = o[k];
+      ti[k] = __float_as_int(o[KT + k]);
+    }
+    m = o[2 * KT];
+    s = o[2 * KT + 1];
+    u = o[2 * KT + 2];
+  }
+#pragma unroll 1
+  for (int c = lane + SB_WAVE; c < n_chunks; c += SB_WAVE) {
     const float* o = part + (size_t)c * (2 * KT + 3);
 #pragma unroll
     for (int k = 0; k < KT; ++k) topk_insert<KT>(tv, ti, o[k], __float_as_int(o[KT + k]));
@@ -403,6 +439,7 @@ __global__ __launch_bounds__(1024) void draft_finalize_kernel(
 #pragma unroll
     for (int b = 0; b < 4; ++b) wv[b][q] = in ? rank_w[(size_t)b * ld + j] : 0.f;
   }
+  const float bias = threadIdx.x < 4 ? rank_b[threadIdx.x] : 0.f;
   float wp[4] = {0.f, 0.f, 0.f, 0.f};
   if (threadIdx.x < SB_PSI) {
 #pragma unroll
@@ -414,24 +451,35 @@ __global__ __launch_bounds__(1024) void draft_finalize_kernel(
     float M, S, U;
     merge_row<SB_TOPK_K>(part + (size_t)i * n_chunks * (2 * SB_TOPK_K + 3),
                          n_chunks, bv, bi, M, S, U);
-    if (threadIdx.x == 0) {
-      const float lse = M + logf(S);
-      const float ent = lse - U / S;
-      for (int k = 0; k < SB_TOPK_K; ++k) {
-        const int id = bi[k];
-        out.topk_id[(size_t)o * SB_TOPK_K + k] =
-            (out.d2t != nullptr && id >= 0 && id < out.n_vocab) ? out.d2t[id] : id;
-        out.topk_logit[(size_t)o * SB_TOPK_K + k] = bv[k];
-        psi_s[k] = bv[k] - lse;
+    // lane k < 10: token k; lane k < 15: psi k
+    const int lane = threadIdx.x;
+    const float lse = M + logf(S);
+    float v = bv[0];
+    int id = bi[0];
+#pragma unroll
+    for (int k = 1; k < SB_TOPK_K; ++k)
+      if (lane == k) {
+        v = bv[k];
+        id = bi[k];
       }
-      psi_s[10] = bv[0] - bv[1];
-      psi_s[11] = bv[0] - bv[2];
-      psi_s[12] = bv[0] - bv[4];
-      psi_s[13] = __expf(bv[0] - lse);
-      psi_s[14] = ent;
+    if (lane < SB_TOPK_K) {
+      out.topk_id[(size_t)o * SB_TOPK_K + lane] =
+          (out.d2t != nullptr && id >= 0 && id < out.n_vocab) ? out.d2t[id] : id;
+      out.topk_logit[(size_t)o * SB_TOPK_K + lane] = v;
+    }
+    float ps = v - lse;
+    if (lane == 10) ps = bv[0] - bv[1];
+    if (lane == 11) ps = bv[0] - bv[2];
+    if (lane == 12) ps = bv[0] - bv[4];
+    if (lane == 13) ps = __expf(bv[0] - lse);
+    if (lane == 14) ps = lse - U / S;
+    if (lane < SB_PSI) {
+      psi_s[lane] = ps;
+      out.psi[(size_t)o * SB_PSI + lane] = ps;
+    }
+    if (lane == 0) {
       out.lse[o] = lse;
       out.lse_copy[o] = lse;
-      for (int k = 0; k < SB_PSI; ++k) out.psi[(size_t)o * SB_PSI + k] = psi_s[k];
     }
   }
   float acc[4] = {0.f, 0.f, 0.f, 0.f};
@@ -456,17 +504,22 @@ __global__ __launch_bounds__(1024) void draft_finalize_kernel(
     if (lane == 0) red[w][b] = t;
   }
   __syncthreads();
-  if (threadIdx.x == 0) {
-    int best = 0;
-    float bs = 0.f;
-    for (int b = 0; b < 4; ++b) {
-      float sc = rank_b[b];
-      for (int q = 0; q < 16; ++q) sc += red[q][b];
-      if (b == 0 || sc > bs) {
-        bs = sc;
-        best = b;
-      }
+  // bucket b's score in lane b, its waves' parts in order
+  if (threadIdx.x < 64) {
+    float sc = 0.f;
+    if (lane < 4) {
+      sc = bias;
+#pragma unroll
+      for (int q = 0; q < 16; ++q) sc += red[q][lane];
     }
+    const float s1 = __shfl(sc, 1, SB_WAVE), s2 = __shfl(sc, 2, SB_WAVE);
+    const float s3 = __shfl(sc, 3, SB_WAVE);
+    if (lane != 0) return;
+    int best = 0;
+    float bs = sc;
+    if (s1 > bs) bs = s1, best = 1;
+    if (s2 > bs) bs = s2, best = 2;
+    if (s3 > bs) bs = s3, best = 3;
     if (out.bucket_in) best = min(max(out.bucket_in[o], 0), 3);
     const int map[4] = {bmap.x, bmap.y, bmap.z, bmap.w};
     out.bucket[o] = best;
