@@ -20,6 +20,10 @@ SOURCES = ["gemm.hip", "elementwise.hip", "attention.hip", "vocab.hip",
            "engine.hip"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = ["--offload-arch=gfx950", "-O3", "-fPIC", "-std=c++17",
+         # kernel arguments (the first 14 dwords) arrive in registers instead
+         # of by a scalar load at the start of every kernel: 25 launches of a
+         # toy model's verification 126.1 -> 121.5 us
+         "-mllvm", "-amdgpu-kernarg-preload-count=16",
          # packed fp32 VALU forms are kept out of the generated code
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
          "-I", os.path.join(ROOT, "include"), "-I", CSRC]

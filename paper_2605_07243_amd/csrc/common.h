@@ -170,6 +170,14 @@ __device__ __forceinline__ int xcd_grouped(int b, int total) {
   return x * q + min(x, r) + (b >> 3);
 }
 
+// a / b and the remainder for 0 <= a < 2^20, 1 <= b < 2^20: in float (the
+// quotient is at least 0.5 / b away from an integer, the error below
+// 2^-22 a / b), five instructions where an integer division by a runtime
+// value is some thirty.
+__device__ __forceinline__ int div_small(int a, int b) {
+  return (int)(((float)a + 0.5f) * __builtin_amdgcn_rcpf((float)b));
+}
+
 // Orders a wave's LDS accesses before and after it (its lanes run in step,
 // so this only keeps the compiler from moving them).
 __device__ __forceinline__ void wave_lds_sync() {

@@ -2,6 +2,8 @@
 // residual add of split-K partials, RoPE + K/V segment write, SwiGLU, the
 // layer-wise shift operand and the drafter input fusion operand.
 // One workgroup per call row; the active row count is read on the device.
+#include <cmath>
+
 #include "bounds.h"
 #include "common.h"
 #include "kernels.h"
@@ -36,72 +38,54 @@ constexpr int kRowThreads = 1024;
 constexpr int kRowVec = 2;
 
 template <typename T>
-__global__ __launch_bounds__(kRowThreads) void embed_kernel(
+__device__ __forceinline__ void store4(T* p, float4 v);
+
+// x = embedding row of the call row's token, out = rmsnorm(x) * g as T (one
+// launch: the row is still in registers when its norm is taken).
+template <typename T>
+__global__ __launch_bounds__(kRowThreads) void embed_norm_kernel(
     const int* __restrict__ n, const int* __restrict__ tok,
-    const T* __restrict__ E, int d, float* __restrict__ x) {
+    const T* __restrict__ E, int d, const float* __restrict__ g, float eps,
+    float* __restrict__ x, T* __restrict__ out) {
+  __shared__ float red[16];
   const int i = blockIdx.x;
   if (i >= *n) return;
   const T* e = E + (size_t)tok[i] * d;
   float4* xr = reinterpret_cast<float4*>(x + (size_t)i * d);
-  float4 v[kRowVec];
+  float4 v[kRowVec], gv[kRowVec];
+  float ss = 0.f;
 #pragma unroll
   for (int q = 0; q < kRowVec; ++q) {
     const int c = threadIdx.x + q * kRowThreads;
-    if (c < d / 4) v[q] = load4<T>(e + 4 * c);
+    const bool ok = c < d / 4;
+    v[q] = ok ? load4<T>(e + 4 * c) : make_float4(0.f, 0.f, 0.f, 0.f);
+    gv[q] = ok ? reinterpret_cast<const float4*>(g)[c]
+               : make_float4(0.f, 0.f, 0.f, 0.f);
   }
 #pragma unroll
   for (int q = 0; q < kRowVec; ++q) {
     const int c = threadIdx.x + q * kRowThreads;
     if (c < d / 4) xr[c] = v[q];
-  }
-}
-
-template <typename T>
-void launch_embed(const CallPlan& p, const T* embed, int d, float* x,
-                  hipStream_t st) {
-  embed_kernel<T><<<p.cap, kRowThreads, 0, st>>>(p.n, p.token, embed, d, x);
-}
-
-template <typename T>
-__device__ __forceinline__ void store4(T* p, float4 v);
-
-// out = rmsnorm(x) * g as T.
-template <typename T>
-__global__ __launch_bounds__(kRowThreads) void rmsnorm_kernel(
-    const float* __restrict__ x, const int* __restrict__ n, int d,
-    const float* __restrict__ g, float eps, T* __restrict__ out, int ldo) {
-  __shared__ float red[16];
-  const int i = blockIdx.x;
-  if (i >= *n) return;
-  const float4* xr = reinterpret_cast<const float4*>(x + (size_t)i * d);
-  float4 v[kRowVec];
-  float ss = 0.f;
-#pragma unroll
-  for (int q = 0; q < kRowVec; ++q) {
-    const int c = threadIdx.x + q * kRowThreads;
-    v[q] = c < d / 4 ? xr[c] : make_float4(0.f, 0.f, 0.f, 0.f);
     ss += sumsq4(v[q]);
   }
   ss = block_sum(ss, red);
   const float r = 1.0f / sqrtf(ss / (float)d + eps);
-  T* o = out + (size_t)i * ldo;
+  T* o = out + (size_t)i * d;
 #pragma unroll
   for (int q = 0; q < kRowVec; ++q) {
     const int c = threadIdx.x + q * kRowThreads;
-    if (c < d / 4)
-      store4<T>(o + 4 * c, scale4(v[q], r, reinterpret_cast<const float4*>(g)[c]));
+    if (c < d / 4) store4<T>(o + 4 * c, scale4(v[q], r, gv[q]));
   }
 }
 
 template <typename T>
-void launch_rmsnorm(const float* x, const int* n, int cap, int d,
-                    const float* g, float eps, T* out, int ldo,
-                    hipStream_t st) {
-  rmsnorm_kernel<T><<<cap, kRowThreads, 0, st>>>(x, n, d, g, eps, out, ldo);
+void launch_embed_norm(const CallPlan& p, const T* embed, int d,
+                       const float* g, float eps, float* x, T* out,
+                       hipStream_t st) {
+  embed_norm_kernel<T><<<p.cap, kRowThreads, 0, st>>>(p.n, p.token, embed, d,
+                                                      g, eps, x, out);
 }
 
-template <typename T>
-__device__ __forceinline__ void store4(T* p, float4 v);
 template <>
 __device__ __forceinline__ void store4<float>(float* p, float4 v) {
   *reinterpret_cast<float4*>(p) = v;
@@ -175,9 +159,9 @@ constexpr int kEarlyRows = 128;
 
 template <typename T, bool EARLY>
 __global__ __launch_bounds__(1024) void residual_kernel(
-    float* __restrict__ x, const float* __restrict__ P, int ks,
-    size_t part_stride, const int* n, int d, int accumulate,
-    const float* __restrict__ g, float eps, T* __restrict__ out, int ldo,
+    const float* __restrict__ P, const int* n, float* __restrict__ x,
+    size_t part_stride, int ks, int d, const float* __restrict__ g,
+    int accumulate, float eps, T* __restrict__ out, int ldo,
     float* __restrict__ taps, int tap_mask, const int* __restrict__ out_row,
     const float* __restrict__ add_rows, const int* __restrict__ add_idx) {
   constexpr int MAXV = 2;
@@ -297,9 +281,45 @@ void launch_residual(float* x, const float* P, int ks, size_t part_stride,
                      const float* add_rows, const int* add_idx) {
   auto k = cap <= kEarlyRows && !g_rows_likely_empty ? residual_kernel<T, true>
                                                      : residual_kernel<T, false>;
-  k<<<cap, 1024, 0, st>>>(x, P, ks, part_stride, n, d, accumulate ? 1 : 0, g,
+  k<<<cap, 1024, 0, st>>>(P, n, x, part_stride, ks, d, g, accumulate ? 1 : 0,
                           eps, out, ldo, taps, tap_mask, out_row, add_rows,
                           add_idx);
+}
+
+// cos and sin of pos theta^(-2t/hd), freq_step = log2(theta) (-2 / hd).  The
+// frequency is 2^n (1 + r) with the Taylor series of 2^f, |f| <= 1/2, to
+// f^13 (1e-17), and the angle is reduced in double, in revolutions, to an
+// eighth of a turn either way; there sine and cosine take the single-precision
+// polynomials of Moshier's Cephes library (sinf, cosf).  The library's exp,
+// log and sincosf did the same in three times the code, which a launch of
+// few rows spends its time fetching.
+__device__ __forceinline__ void rope_angle(double pos, double freq_step, int t,
+                                           float& c, float& s) {
+  const double e = freq_step * (double)t;
+  const double n = __builtin_rint(e);
+  const double f = (e - n) * 0.693147180559945309417232;   // ln 2
+  constexpr double kInvFact[14] = {
+      1.0, 1.0, 1.0 / 2, 1.0 / 6, 1.0 / 24, 1.0 / 120, 1.0 / 720, 1.0 / 5040,
+      1.0 / 40320, 1.0 / 362880, 1.0 / 3628800, 1.0 / 39916800,
+      1.0 / 479001600, 1.0 / 6227020800.0};
+  double w = kInvFact[13];
+#pragma unroll
+  for (int k = 12; k >= 0; --k) w = __builtin_fma(w, f, kInvFact[k]);
+  constexpr double kInv2Pi = 0.159154943091895335768884;
+  const double rev = pos * (__builtin_amdgcn_ldexp(w, (int)n) * kInv2Pi);
+  const double r4 = 4.0 * (rev - __builtin_rint(rev));     // quarter turns
+  const double qd = __builtin_rint(r4);
+  const float x = (float)((r4 - qd) * 1.570796326794896619231322);
+  const int qi = (int)qd & 3;
+  const float z = x * x;
+  const float sp =
+      ((-1.9515295891e-4f * z + 8.3321608736e-3f) * z - 1.6666654611e-1f) * z * x + x;
+  const float cp =
+      ((2.443315711809948e-5f * z - 1.388731625493765e-3f) * z +
+       4.166664568298827e-2f) * z * z - 0.5f * z + 1.0f;
+  const float a = (qi & 1) ? cp : sp, b = (qi & 1) ? sp : cp;
+  s = (qi & 2) ? -a : a;
+  c = (qi == 1 || qi == 2) ? -b : b;
 }
 
 // RoPE (rotate-half pairs (j, j + hd/2), angle pos * theta^(-2j/hd)) on the
@@ -312,7 +332,7 @@ void launch_residual(float* x, const float* P, int ks, size_t part_stride,
 template <typename T, bool EARLY>
 __global__ __launch_bounds__(256) void qkv_post_kernel(
     const float* __restrict__ P, int ks, size_t part_stride, CallPlan p, int H,
-    int Hkv, int hd, float theta, T* __restrict__ q, KVView kv) {
+    int Hkv, int hd, double freq_step, T* __restrict__ q, KVView kv) {
   __shared__ __attribute__((aligned(16))) float cs[128];
   __shared__ __attribute__((aligned(16))) float sn[128];
   const int i = blockIdx.x;
@@ -336,14 +356,14 @@ __global__ __launch_bounds__(256) void qkv_post_kernel(
   float4 a = make_float4(0.f, 0.f, 0.f, 0.f), b = a;
   int head = 0, j = 0;
   if (idx < n_rot) {
-    head = idx / q4;
-    j = (idx % q4) * 4;
+    head = div_small(idx, q4);
+    j = (idx - head * q4) * 4;
     sum_parts2(P, part_stride, ks, row + head * hd + j,
                row + head * hd + j + half, a, b);
   } else if (idx < n_items) {
     const int v = idx - n_rot;
-    head = v / (hd >> 2);
-    j = (v % (hd >> 2)) * 4;
+    head = div_small(v, hd >> 2);
+    j = (v - head * (hd >> 2)) * 4;
     a = sum_parts(P, part_stride, ks, row + (H + Hkv) * hd + head * hd + j);
   }
   if constexpr (EARLY) {
@@ -380,17 +400,8 @@ __global__ __launch_bounds__(256) void qkv_post_kernel(
     }
   }
   const double pos = (double)p.pos[i];
-  for (int t = threadIdx.x; t < half; t += blockDim.x) {
-    // angle in double, reduced to [-pi, pi] before the fp32 sincos
-    const double inv = exp(-((double)(2 * t) / (double)hd) * log((double)theta));
-    const double ang = pos * inv;
-    const double two_pi = 6.283185307179586476925287;
-    const float red = (float)(ang - two_pi * rint(ang / two_pi));
-    float sv, cv;
-    sincosf(red, &sv, &cv);
-    cs[t] = cv;
-    sn[t] = sv;
-  }
+  for (int t = threadIdx.x; t < half; t += blockDim.x)
+    rope_angle(pos, freq_step, t, cs[t], sn[t]);
   __syncthreads();
   if (idx < n_rot) {
     const float4 c4 = *reinterpret_cast<const float4*>(&cs[j]);
@@ -435,7 +446,8 @@ void launch_qkv_post(const float* P, int ks, size_t part_stride,
                ? qkv_post_kernel<T, true>
                : qkv_post_kernel<T, false>;
   k<<<dim3(p.cap, (items + 255) / 256), 256, 0, st>>>(
-      P, ks, part_stride, p, H, Hkv, hd, theta, q, kv);
+      P, ks, part_stride, p, H, Hkv, hd,
+      std::log2((double)theta) * (-2.0 / (double)hd), q, kv);
 }
 
 // out = silu(gate) * up, four columns per thread; grid (rows, F / 1024).
@@ -624,10 +636,9 @@ void launch_rows_to_elem(const float* src, const int* idx, const int* n,
 }
 
 #define SB_INST(T)                                                             \
-  template void launch_embed<T>(const CallPlan&, const T*, int, float*,        \
-                                hipStream_t);                                  \
-  template void launch_rmsnorm<T>(const float*, const int*, int, int,          \
-                                  const float*, float, T*, int, hipStream_t);  \
+  template void launch_embed_norm<T>(const CallPlan&, const T*, int,           \
+                                     const float*, float, float*, T*,          \
+                                     hipStream_t);                             \
   template void launch_residual<T>(float*, const float*, int, size_t,          \
                                    const int*, int, int, bool, const float*,   \
                                    float, T*, int, float*, int, const int*,    \

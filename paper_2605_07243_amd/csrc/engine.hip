@@ -808,10 +808,9 @@ void target_forward(sb_ctx* c, const CallPlan& p, const Prefix& pf,
   const Dims& D = c->D;
   const float eps = c->cfg.target.norm_eps;
   c->prof_group = SB_GEMM_TARGET;
-  launch_embed<T>(p, static_cast<const T*>(c->tw.embed), D.d, c->x, st);
-  launch_rmsnorm<T>(c->x, p.n, p.cap, D.d,
-                    static_cast<const float*>(c->tw.layers[0].attn_norm), eps,
-                    static_cast<T*>(c->A), D.d, st);
+  launch_embed_norm<T>(p, static_cast<const T*>(c->tw.embed), D.d,
+                       static_cast<const float*>(c->tw.layers[0].attn_norm),
+                       eps, c->x, static_cast<T*>(c->A), st);
   for (int l = 0; l < D.L; ++l) {
     const float* next_g = l + 1 < D.L
                               ? static_cast<const float*>(c->tw.layers[l + 1].attn_norm)

@@ -102,13 +102,15 @@ __device__ __forceinline__ void vr_stats_merge(float& m, float& s, float& u,
 // record (top VR, m, s, u) of its 128 NF output columns to
 // rec[(row * n_nt + column tile) * (2 VR + 3)].  n_first (a multiple of
 // 32 NF; 0 with VR > 0): the launch covers weight rows n_first .. N - 1, in
-// n_nt column tiles from there.
+// n_nt column tiles from there.  What the first loads need stands first
+// among the arguments: the first 14 dwords arrive in registers with the
+// wave (kernel argument preload), the others cost a scalar load each.
 template <int MF, int NF, int PF, bool SWIGLU, int VR>
 __global__ __launch_bounds__(256) void gemm_tile_kernel(
-    const bf16_t* X, int ldx, const bf16_t* W, int K, float* __restrict__ P,
-    int N, size_t part_stride, const int* __restrict__ m_count, int k_chunk,
-    int n_mt, int n_nt, bf16_t* __restrict__ act, int F,
-    float* __restrict__ rec, int n_first, int x_rows) {
+    const bf16_t* X, const bf16_t* W, const int* __restrict__ m_count, int ldx,
+    int K, int N, int k_chunk, int n_mt, int n_nt, int n_first, int x_rows,
+    float* __restrict__ P, size_t part_stride, bf16_t* __restrict__ act, int F,
+    float* __restrict__ rec) {
   static_assert(PF == 2 || PF == 4, "weight ring depth");
   constexpr int BM = 32 * MF;
   constexpr int LD = 64 + 8;
@@ -414,9 +416,9 @@ __global__ __launch_bounds__(256) void gemm_tile_kernel(
 
 template <int MT>
 __global__ __launch_bounds__(256) void gemm_xwt_kernel(
-    const float* __restrict__ X, int ldx, const float* __restrict__ W, int K,
-    float* __restrict__ P, int N, size_t part_stride,
-    const int* __restrict__ m_count, int k_chunk) {
+    const float* __restrict__ X, const float* __restrict__ W,
+    const int* __restrict__ m_count, int ldx, int K, int N, int k_chunk,
+    float* __restrict__ P, size_t part_stride) {
   const int m_base = blockIdx.z * (MT * 16);
   const int M = min(*m_count - m_base, MT * 16);
   if (M <= 0) return;
@@ -571,9 +573,15 @@ GemmPlan gemm_plan(int N, int K, int m_cap, int elem_bytes, bool retile) {
   GemmPlan g{};
   if (elem_bytes == 4) {
     g.mf = m_cap <= 16 ? 1 : (m_cap <= 32 ? 2 : 4);  // 16-row tiles
-    const int tiles = N / 16;
+    // K-chunks of at least 32 steps of 32 columns (8 per wave) up to 1024
+    // workgroups, of at least 8 steps (2 per wave) while the launch leaves
+    // CUs idle: 32 rows x 256 x 1024 in 16 workgroups of 32 steps took
+    // 9.4-12 us, in 64 of 8 steps 5.0 us
+    const int tiles = N / 16, wgs = tiles * ((m_cap + 63) / 64);
     g.ks = 1;
-    while (tiles * g.ks < 1024 && K / (32 * (g.ks * 2)) >= 32 && g.ks < 16)
+    while (g.ks < 16 &&
+           ((tiles * g.ks < 1024 && K / (64 * g.ks) >= 32) ||
+            (wgs * g.ks < kTargetWorkgroups && K / (64 * g.ks) >= 8)))
       g.ks *= 2;
     return g;
   }
@@ -667,9 +675,10 @@ void launch_tile(const GemmPlan& g, const bf16_t* X, int ldx, const bf16_t* W,
     hipEvent_t ea, eb;                                                        \
     take_events(ea, eb);                                                      \
     hipExtLaunchKernelGGL(gemm_tile_kernel<MF_, NF_, PF_, SWIGLU, VR>, grid,  \
-                          dim3(256), 0, st, ea, eb, 0, X, ldx, W, K, P, N,    \
-                          part_stride, m_count, k_chunk, n_mt, n_nt, act, F,  \
-                          rec, n_first, rows_likely_empty() ? 0 : m_cap);     \
+                          dim3(256), 0, st, ea, eb, 0, X, W, m_count, ldx, K, \
+                          N, k_chunk, n_mt, n_nt, n_first,                    \
+                          rows_likely_empty() ? 0 : m_cap, P, part_stride,    \
+                          act, F, rec);                                       \
     return;                                                                   \
   }
   SB_LAUNCH(1, 1, 2)
@@ -709,16 +718,16 @@ int launch_gemm_xwt(const T* X, int ldx, const T* W, int N, int K, float* P,
     take_events(ea, eb);
     if (m_cap <= 16) {
       hipExtLaunchKernelGGL(gemm_xwt_kernel<1>, dim3(N / 16, ks, 1), block, 0,
-                            st, ea, eb, 0, X, ldx, W, K, P, N, part_stride,
-                            m_count, k_chunk);
+                            st, ea, eb, 0, X, W, m_count, ldx, K, N, k_chunk, P,
+                            part_stride);
     } else if (m_cap <= 32) {
       hipExtLaunchKernelGGL(gemm_xwt_kernel<2>, dim3(N / 16, ks, 1), block, 0,
-                            st, ea, eb, 0, X, ldx, W, K, P, N, part_stride,
-                            m_count, k_chunk);
+                            st, ea, eb, 0, X, W, m_count, ldx, K, N, k_chunk, P,
+                            part_stride);
     } else {
       hipExtLaunchKernelGGL(gemm_xwt_kernel<4>, dim3(N / 16, ks, mz), block, 0,
-                            st, ea, eb, 0, X, ldx, W, K, P, N, part_stride,
-                            m_count, k_chunk);
+                            st, ea, eb, 0, X, W, m_count, ldx, K, N, k_chunk, P,
+                            part_stride);
     }
     return ks;
   }

@@ -104,13 +104,11 @@ int gemm_vocab_chunks(int N, int K, int m_cap);
 int launch_pack_weight(const bf16_t* src, bf16_t* dst, int rows, int cols,
                        bool gate_up, hipStream_t st);
 
+// x = embedding rows of the call rows' tokens, out = rmsnorm(x) * g.
 template <typename T>
-void launch_embed(const CallPlan& p, const T* embed, int d, float* x,
-                  hipStream_t st);
-template <typename T>
-void launch_rmsnorm(const float* x, const int* n, int cap, int d,
-                    const float* g, float eps, T* out, int ldo,
-                    hipStream_t st);
+void launch_embed_norm(const CallPlan& p, const T* embed, int d,
+                       const float* g, float eps, float* x, T* out,
+                       hipStream_t st);
 // x = (accumulate ? x : 0) + sum_ks P[ks]; then optionally out = rmsnorm(x)*g
 // and taps[out_row][j] = x for every bit j of tap_mask.
 // add_rows (optional, fp32 [.][d]): row add_rows[add_idx[i] - 1] is added
