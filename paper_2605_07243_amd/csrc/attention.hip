@@ -55,11 +55,17 @@ __device__ __forceinline__ uint4 keep_slots(uint4 v, int first, int nvalid) {
 // workgroup writes (O, m, l) partials that attn_merge combines; with one
 // split the kernel writes the output.
 //
+// KS > 1: KS groups of NQ waves share the workgroup's q-tiles and take the
+// split's tiles in turn (group g tiles g, g + KS, ...), each with its own
+// LDS buffers; group 0 combines the groups' (O, m, l) through LDS at the
+// end.  A workgroup of few tiles is a serial chain of tile latencies (1.5 to
+// 2 us each), so this is the form for launches of few workgroups.
+//
 // CAUSAL (prefill pieces, see CallPlan::kv_row): s is a piece, all of its
 // keys are in the paged cache (no segment), and a row attends to the entries
 // up to its own, kv_dst.
-template <typename T, int HD, int NQ, int QT, bool CAUSAL>
-__global__ __launch_bounds__(NQ * 64) void tree_attn_kernel(
+template <typename T, int HD, int NQ, int QT, int KS, bool CAUSAL>
+__global__ __launch_bounds__(NQ * KS * 64) void tree_attn_kernel(
     const T* __restrict__ q, CallPlan p, KVView kv, int H, int Hkv,
     int split_tokens, float scale, float* __restrict__ o_part,
     float* __restrict__ ml, T* __restrict__ out, int key_cap) {
@@ -73,8 +79,9 @@ __global__ __launch_bounds__(NQ * 64) void tree_attn_kernel(
   constexpr int NT = NQ * 64;
   constexpr int PER = (KCH + VCH + NT - 1) / NT;
   constexpr int QPW = NQ * QT;                      // q-tiles per workgroup
-  __shared__ __attribute__((aligned(16))) T ksh[2][32][LDK];
-  __shared__ __attribute__((aligned(16))) T vsh[2][HD][LDV];
+  // one group's buffers: two K tiles, then two V^T tiles
+  constexpr int GRP = 2 * (32 * LDK + HD * LDV);
+  __shared__ __attribute__((aligned(16))) T tiles_sh[KS][GRP];
   // XCD-grouped order: the dispatcher deals workgroups out round-robin over
   // the 8 XCDs, so neighbouring ids would land on different XCDs and each
   // fetch the same K/V or Q into its own L2.  Remapped, a run of consecutive
@@ -98,7 +105,11 @@ __global__ __launch_bounds__(NQ * 64) void tree_attn_kernel(
   const int nq = (p.seq_off[s + 1] - row0) * G;
   const int qg = bx;
   if (qg * QPW * 16 >= nq) return;                  // uniform for the group
-  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+  const int grp = KS == 1 ? 0 : threadIdx.x / NT;   // wave-uniform
+  const int tid = threadIdx.x - grp * NT, wave = tid >> 6, lane = tid & 63;
+  T(*ksh)[32][LDK] = reinterpret_cast<T(*)[32][LDK]>(&tiles_sh[grp][0]);
+  T(*vsh)[HD][LDV] =
+      reinterpret_cast<T(*)[HD][LDV]>(&tiles_sh[grp][2 * 32 * LDK]);
   const int r = lane & 15, g = lane >> 4;
   bool qvalid[QT], live[QT];
   int qrow[QT], qh[QT];
@@ -160,7 +171,7 @@ __global__ __launch_bounds__(NQ * 64) void tree_attn_kernel(
   __shared__ int pg_sh[MAXP];
   const int pg0 = t0 >> 4;
   const int n_pg = t1 > t0 ? ((t1 + 15) >> 4) - pg0 : 0;
-  for (int j = tid; j < n_pg && j < MAXP; j += NT)
+  for (int j = threadIdx.x; j < n_pg && j < MAXP; j += NT * KS)
     pg_sh[j] = checked_index(ptab[pg0 + j], kv.n_pages, kv.err, kDevPage);
   __syncthreads();
 
@@ -183,7 +194,7 @@ __global__ __launch_bounds__(NQ * 64) void tree_attn_kernel(
   // values are used raw until the stash / compute of the tile (an empty
   // half reads page 0: its keys are masked and its V slots zeroed there),
   // so no load is consumed before its turn and the ring stays in flight.
-  constexpr int DEPTH = 4;
+  constexpr int DEPTH = KS == 1 ? 4 : 2;
   uint4 stg[DEPTH][PER];
   uint32_t visr[DEPTH][QT];
   auto fetch = [&](int i, uint4 (&dst)[PER], uint32_t (&vdst)[QT]) {
@@ -314,25 +325,64 @@ __global__ __launch_bounds__(NQ * 64) void tree_attn_kernel(
     }
   };
   if (n_tiles > 0) {
+    // this group's u-th tile is u KS + grp; every group runs the same rounds
+    auto at = [&](int u) { return u * KS + grp; };
+    const int rounds = (n_tiles + KS - 1) / KS;
 #pragma unroll
-    for (int d = 0; d < DEPTH; ++d) fetch(min(d, n_tiles - 1), stg[d], visr[d]);
-    stash(0, 0, stg[0]);
+    for (int d = 0; d < DEPTH; ++d)
+      fetch(min(at(d), n_tiles - 1), stg[d], visr[d]);
+    if (at(0) < n_tiles) stash(at(0), 0, stg[0]);
     __syncthreads();
-    // tile i lives in slot i % DEPTH; after it is stashed the slot is
-    // refilled with tile i + DEPTH (the last tile again past the end); its
+    // the u-th tile lives in slot u % DEPTH; after it is stashed the slot is
+    // refilled with tile u + DEPTH (the last tile again past the end); its
     // visibility words are copied out before the refill
-    for (int i0 = 0; i0 < n_tiles; i0 += DEPTH) {
+    for (int u0 = 0; u0 < rounds; u0 += DEPTH) {
 #pragma unroll
       for (int d = 0; d < DEPTH; ++d) {
-        const int i = i0 + d;
+        const int u = u0 + d;
         uint32_t vword[QT];
 #pragma unroll
         for (int j = 0; j < QT; ++j) vword[j] = CAUSAL ? 0u : visr[d][j];
-        fetch(min(i + DEPTH, n_tiles - 1), stg[d], visr[d]);
-        if (i < n_tiles) compute(i, i & 1, vword);
-        if (i + 1 < n_tiles) stash(i + 1, (i + 1) & 1, stg[(d + 1) % DEPTH]);
+        fetch(min(at(u + DEPTH), n_tiles - 1), stg[d], visr[d]);
+        if (at(u) < n_tiles) compute(at(u), u & 1, vword);
+        if (at(u + 1) < n_tiles)
+          stash(at(u + 1), (u + 1) & 1, stg[(d + 1) % DEPTH]);
         __syncthreads();
       }
+    }
+  }
+  if constexpr (KS > 1) {
+    // the other groups' (O, m, l) of every lane, lane-contiguous, in the tile
+    // buffers (all waves are past the last barrier, so no tile is read again)
+    static_assert(QT == 1, "one q-tile per wave with key groups");
+    constexpr int NV = HD / 4 + 2;
+    static_assert((size_t)(KS - 1) * NQ * NV * 64 * 4 <= sizeof(tiles_sh),
+                  "group partials fit the tile buffers");
+    float* part = reinterpret_cast<float*>(&tiles_sh[0][0]);
+    if (grp > 0) {
+      float* o = part + (size_t)((grp - 1) * NQ + wave) * NV * 64 + lane;
+#pragma unroll
+      for (int c = 0; c < HD / 16; ++c)
+#pragma unroll
+        for (int rr = 0; rr < 4; ++rr) o[(4 * c + rr) * 64] = acc[0][c][rr];
+      o[(NV - 2) * 64] = m_run[0];
+      o[(NV - 1) * 64] = l_run[0];
+    }
+    __syncthreads();
+    if (grp > 0) return;
+#pragma unroll
+    for (int k = 1; k < KS; ++k) {
+      const float* o = part + (size_t)((k - 1) * NQ + wave) * NV * 64 + lane;
+      const float mk = o[(NV - 2) * 64], lk = o[(NV - 1) * 64];
+      const float m_new = fmaxf(m_run[0], mk);
+      const float a0 = __expf(m_run[0] - m_new), a1 = __expf(mk - m_new);
+      l_run[0] = l_run[0] * a0 + lk * a1;
+      m_run[0] = m_new;
+#pragma unroll
+      for (int c = 0; c < HD / 16; ++c)
+#pragma unroll
+        for (int rr = 0; rr < 4; ++rr)
+          acc[0][c][rr] = acc[0][c][rr] * a0 + o[(4 * c + rr) * 64] * a1;
     }
   }
 
@@ -1035,22 +1085,39 @@ void launch_tree_attn(const T* q, const CallPlan& p, const KVView& kv,
     }
   }
   {
-#define SB_ATTN(HD_, NQ_, QT_)                                                 \
-  if (hd == HD_ && a.nq == NQ_ && a.qt == QT_) {                              \
-    auto k = p.kv_row != nullptr ? tree_attn_kernel<T, HD_, NQ_, QT_, true>   \
-                                 : tree_attn_kernel<T, HD_, NQ_, QT_, false>; \
-    hipExtLaunchKernelGGL(k, grid,                                            \
-                          dim3(NQ_ * 64), 0, st, ka, kb, 0, q, p, kv, H, Hkv, \
-                          split_tokens, scale, o_part, ml, out, max_prefix);  \
+#define SB_ATTN(HD_, NQ_, QT_, KS_)                                            \
+  if (hd == HD_ && a.nq == NQ_ && a.qt == QT_ && ks == KS_) {                 \
+    auto k = p.kv_row != nullptr                                              \
+                 ? tree_attn_kernel<T, HD_, NQ_, QT_, KS_, true>              \
+                 : tree_attn_kernel<T, HD_, NQ_, QT_, KS_, false>;            \
+    hipExtLaunchKernelGGL(k, grid, dim3(NQ_ * KS_ * 64), 0, st, ka, kb, 0, q, \
+                          p, kv, H, Hkv, split_tokens, scale, o_part, ml,     \
+                          out, max_prefix);                                   \
     if (n_split > 1)                                                          \
       launch_attn_merge<T>(p, H, hd, n_split, o_part, ml, out, st, eb);       \
     return;                                                                   \
   }
-    if constexpr (sizeof(T) == 2) SB_ATTN(128, 8, 2)
-    SB_ATTN(128, 8, 1) SB_ATTN(128, 4, 1) SB_ATTN(128, 2, 1)
-    if constexpr (sizeof(T) == 2) SB_ATTN(128, 1, 1)
-    SB_ATTN(64, 8, 2) SB_ATTN(64, 8, 1) SB_ATTN(64, 4, 1)
-    SB_ATTN(64, 2, 1) SB_ATTN(64, 1, 1)
+    // key groups (see the kernel) when the launch leaves three CUs in four
+    // without a workgroup: eight waves each, as far as the groups' tiles fit
+    // the LDS (fp32 tiles of 128-wide heads: two groups).  Measured, per
+    // call: 4 workgroups of two waves over 5 tiles (fp32, 64-wide heads) 17.3
+    // -> 12.5 us; 256 workgroups of four waves (60 nodes over 1024 keys)
+    // slower, 1188 -> 1209 us for the verification around it
+    const bool few = (long)grid.x * grid.y * grid.z <= kAttnSlots / 4;
+    const int ks = !few || a.qt > 1 || a.nq > 4 ? 1
+                   : a.nq == 4 || (sizeof(T) == 4 && hd == 128) ? 2
+                                                                : 4;
+    if constexpr (sizeof(T) == 2) SB_ATTN(128, 8, 2, 1)
+    SB_ATTN(128, 8, 1, 1) SB_ATTN(128, 4, 1, 1) SB_ATTN(128, 2, 1, 1)
+    SB_ATTN(128, 4, 1, 2)
+    if constexpr (sizeof(T) == 2) {
+      SB_ATTN(128, 1, 1, 1) SB_ATTN(128, 2, 1, 4) SB_ATTN(128, 1, 1, 4)
+    } else {
+      SB_ATTN(128, 2, 1, 2)
+    }
+    SB_ATTN(64, 8, 2, 1) SB_ATTN(64, 8, 1, 1) SB_ATTN(64, 4, 1, 1)
+    SB_ATTN(64, 2, 1, 1) SB_ATTN(64, 1, 1, 1)
+    SB_ATTN(64, 4, 1, 2) SB_ATTN(64, 2, 1, 4) SB_ATTN(64, 1, 1, 4)
 #undef SB_ATTN
   }
 }
