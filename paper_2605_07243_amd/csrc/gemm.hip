@@ -285,24 +285,7 @@ __global__ __launch_bounds__(256) void gemm_tile_kernel(
       }
       float mx = -FLT_MAX, sm = 0.f, su = 0.f;
       if (wave_on) {
-        // lane register r of fragment f is column nb + 32 f + 8 (r / 4) +
-        // 4 h + r % 4 of row m
-#pragma unroll
-        for (int f = 0; f < NF; ++f)
-#pragma unroll
-          for (int r = 0; r < 16; ++r) {
-            const float v = acc[t][f][r];
-            mx = fmaxf(mx, v);
-            vr_insert<VR>(tv, ti, v, nb + 32 * f + 8 * (r >> 2) + 4 * h + (r & 3));
-          }
-#pragma unroll
-        for (int f = 0; f < NF; ++f)
-#pragma unroll
-          for (int r = 0; r < 16; ++r) {
-            const float e = __expf(acc[t][f][r] - mx);
-            sm += e;
-            su = fmaf(e, acc[t][f][r], su);
-          }
+        // the logits go out first: their stores drain under the statistics
         if (P != nullptr && m < M) {
 #pragma unroll
           for (int f = 0; f < NF; ++f)
@@ -312,6 +295,30 @@ __global__ __launch_bounds__(256) void gemm_tile_kernel(
                   make_float4(acc[t][f][4 * q], acc[t][f][4 * q + 1],
                               acc[t][f][4 * q + 2], acc[t][f][4 * q + 3]);
         }
+        // lane register r of fragment f is column nb + 32 f + 8 (r / 4) +
+        // 4 h + r % 4 of row m, ascending in (f, r): the first maximum is the
+        // last one found from behind
+        static_assert(VR == 1, "top-1 records");
+#pragma unroll
+        for (int f = 0; f < NF; ++f)
+#pragma unroll
+          for (int r = 0; r < 16; ++r) mx = fmaxf(mx, acc[t][f][r]);
+        int at = -1;
+#pragma unroll
+        for (int f = NF - 1; f >= 0; --f)
+#pragma unroll
+          for (int r = 15; r >= 0; --r)
+            at = acc[t][f][r] == mx ? 32 * f + 8 * (r >> 2) + (r & 3) : at;
+        tv[0] = mx;
+        if (at >= 0) ti[0] = nb + 4 * h + at;
+#pragma unroll
+        for (int f = 0; f < NF; ++f)
+#pragma unroll
+          for (int r = 0; r < 16; ++r) {
+            const float e = __expf(acc[t][f][r] - mx);
+            sm += e;
+            su = fmaf(e, acc[t][f][r], su);
+          }
       }
       // the lane pair (h = 0, 1) holds the same row
       {
