@@ -49,7 +49,7 @@ __device__ __forceinline__ uint4 keep_slots(uint4 v, int first, int nvalid) {
 // (q-tile j of wave w is tile group * NQ * QT + j * NQ + w) and one split of
 // the prefix (the last split also takes the segment).  K and V tiles of 32
 // keys are staged once per workgroup in LDS (double buffered; global loads
-// run four tiles ahead in registers) and read by every wave; a wave reuses
+// run two tiles ahead in registers) and read by every wave; a wave reuses
 // every K and V operand it reads for its QT q-tiles, so a split's K/V is
 // read once for up to 16 NQ QT query vectors.  With several splits each
 // workgroup writes (O, m, l) partials that attn_merge combines; with one
@@ -194,7 +194,9 @@ __global__ __launch_bounds__(NQ * KS * 64) void tree_attn_kernel(
   // values are used raw until the stash / compute of the tile (an empty
   // half reads page 0: its keys are masked and its V slots zeroed there),
   // so no load is consumed before its turn and the ring stays in flight.
-  constexpr int DEPTH = KS == 1 ? 4 : 2;
+  // (two: with four the unrolled loop was 17 KB of code, fetched anew by
+  // every launch; 8 layers over 1024 keys 1193 -> 1179 us)
+  constexpr int DEPTH = 2;
   uint4 stg[DEPTH][PER];
   uint32_t visr[DEPTH][QT];
   auto fetch = [&](int i, uint4 (&dst)[PER], uint32_t (&vdst)[QT]) {
@@ -524,7 +526,11 @@ __global__ __launch_bounds__(NW * 64) void tree_attn32_kernel(
   constexpr int PER = (CH + NT - 1) / NT;
   constexpr int HB = HD / 32;               // head_dim blocks of 32
   constexpr int QK = HD / 16;               // contraction steps of S^T
-  constexpr int DEPTH = NW >= 8 ? 1 : 3;     // staging registers: 16 PER each
+  // one tile of global loads in flight: a compute phase covers most of their
+  // latency, and a launch of few tiles spends its time fetching the loop's
+  // code (with three tiles in flight the 4-wave kernel was 38 KB; first block
+  // of 16 sequences 468 -> 459 us, commit with 16 catch-up rows 284 -> 279)
+  constexpr int DEPTH = 1;
   __shared__ __attribute__((aligned(16))) bf16_t ksh[2][KT][LDK];
   __shared__ __attribute__((aligned(16))) bf16_t vsh[2][HD][LDV];
   constexpr int MAXP = 1024;

@@ -773,8 +773,8 @@ void layer_body(sb_ctx* c, const sb_layer_weights& lw, int layer,
                                           : cap_tokens;
   const int G = D.H / D.Hkv, seq_heads = p.n_seqs * D.Hkv;
   const int groups = attn_qgroups(rows_per_seq, G, seq_heads, D.es) * seq_heads;
-  // enough workgroups for the chip, splits of at least 128 keys (the
-  // kernel keeps four 32-key tiles in flight; shorter splits measured slower)
+  // enough workgroups for the chip, splits of at least 128 keys (shorter
+  // ones measured slower)
   int n_split = std::max(
       1, ceil_div(attn_workgroup_target(rows_per_seq, G, seq_heads, D.es), groups));
   n_split = std::min(n_split, std::max(1, max_prefix / 128));
