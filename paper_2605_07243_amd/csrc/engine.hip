@@ -1018,6 +1018,9 @@ int commit_impl(sb_ctx* c, sb_seqs* sq, const sb_tree* t,
                    dkv->n_pages, c->dseg_k, c->dseg_v, D.dpages, c->dbg()};
   launch_commit_apply<T>(td, *t, *acc, c->ci, tp, D.L, dp, D.LD, D.S, D.Hkv,
                          D.hd, *sq, v->taps, st);
+  // raised before the catch-up forward: its rows attend to the entries that
+  // this commit adds
+  if (c->T_bound > 0) c->T_bound += D.M * D.K + 1;
   // catch-up rows where the tree has no row continuing the accepted path
   // (usually none: its launches test the live count before loading)
   set_rows_likely_empty(true);
@@ -1027,7 +1030,6 @@ int commit_impl(sb_ctx* c, sb_seqs* sq, const sb_tree* t,
   fb.cap = sq->n_seqs;
   drafter_forward<T>(c, fb, c->cond_buf, pf, 1, false, st);
   set_rows_likely_empty(false);
-  if (c->T_bound > 0) c->T_bound += D.M * D.K + 1;
   return hip_check(c, "sb_commit");
 }
 
