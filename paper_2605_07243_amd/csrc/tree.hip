@@ -238,13 +238,14 @@ __global__ __launch_bounds__(64) void attach_kernel(
   if (is_end && e_excl < td.B_max) out[e_excl] = chain;
   int taken = min(n_ends, td.B_max);
   // candidates of a lane: nodes first_new + lane + 64 q (values in registers;
-  // most blocks add at most 64 nodes, and then one round of q is all)
+  // most blocks add at most 64 nodes, and then one round of q is all); a NaN
+  // is no candidate and must not hide the lane's others below
   const int nq = (nn - first_new + 63) >> 6;
   float cand[8];
 #pragma unroll
   for (int q = 0; q < 8; ++q) {
     const int j = lane + 64 * q;
-    cand[q] = q < nq && first_new + j < nn ? cand_s[j] : -FLT_MAX;
+    cand[q] = q < nq && first_new + j < nn ? fmaxf(cand_s[j], -FLT_MAX) : -FLT_MAX;
   }
 #pragma unroll 1
   while (taken < td.B_max) {
