@@ -83,8 +83,10 @@ typedef struct sb_config {
   int32_t page_size;        /* K/V page size in tokens; must be 16            */
   int32_t max_pages;        /* page-table row length (pages per sequence),
                                1..16384                                       */
-  int32_t prefill_chunk;    /* 16..512, a multiple of 16; no longer read: a
-                               prefill runs in passes of up to 2048 rows      */
+  int32_t prefill_chunk;    /* prompt rows per prefill pass in the least
+                               workspace (16..512, a multiple of 16); a larger
+                               one makes the passes longer, see
+                               sb_workspace_bytes_prefill                     */
   int32_t draft_vocab;      /* drafter output vocabulary: 0 = the target's;
                                else a multiple of 16 in 10..vocab, the
                                drafter's reduced vocabulary (App. A: the most
@@ -226,6 +228,11 @@ typedef struct sb_ctx sb_ctx;
 int32_t sb_row_capacity(const sb_config* cfg);
 /* Workspace bytes sb_bind needs for this configuration (0 if invalid). */
 size_t sb_workspace_bytes(const sb_config* cfg);
+/* Workspace bytes with which a prefill runs in passes of up to prefill_rows
+ * prompt rows (0 if the configuration is invalid).  Every pass streams all
+ * weights once, so longer passes are faster, up to 2048 rows, the most that
+ * a pass takes; fewer rows than cfg.prefill_chunk count as that many. */
+size_t sb_workspace_bytes_prefill(const sb_config* cfg, int32_t prefill_rows);
 
 /* Validate cfg (SB_EINVAL / SB_ESHAPE / SB_EDTYPE) and create a context.
  * The configuration carries the inputs of one verifier iteration (Alg. 2:
@@ -248,7 +255,8 @@ const char* sb_last_error(const sb_ctx* ctx);
  * freed); the device memory they point to must outlive the context.
  * workspace: device, 256-byte aligned, >= sb_workspace_bytes(cfg) bytes,
  * owned by the caller and used as the library's scratch until the context
- * is destroyed or bound again.  Errors: SB_EINVAL (NULL or misaligned
+ * is destroyed or bound again; what it has beyond that lengthens the prefill
+ * passes (sb_workspace_bytes_prefill).  Errors: SB_EINVAL (NULL or misaligned
  * pointers, a d2t that is not strictly increasing in [0, vocab)),
  * SB_EBUDGET (workspace too small), SB_EHIP (reading d2t failed).
  * SB_BF16: the projection matrices must have been packed by sb_pack_weight

@@ -116,7 +116,8 @@ class GemmStat(C.Structure):
 PROF_CLASSES = ("gemm", "tree_attn", "vocab")
 GEMM_GROUPS = ("target", "drafter", "swiglu", "lm_head")
 
-EXPORTS = ["sb_row_capacity", "sb_workspace_bytes", "sb_create", "sb_destroy",
+EXPORTS = ["sb_row_capacity", "sb_workspace_bytes",
+           "sb_workspace_bytes_prefill", "sb_create", "sb_destroy",
            "sb_last_error", "sb_bind", "sb_prefill", "sb_draft_block_expand",
            "sb_tree_verify", "sb_accept", "sb_commit", "sb_set_length_bound",
            "sb_profile", "sb_profile_read", "sb_profile_read_gemm",
@@ -143,6 +144,8 @@ def load(path: str = LIB_PATH):
     lib.sb_row_capacity.restype = i32
     lib.sb_workspace_bytes.argtypes = [P(Config)]
     lib.sb_workspace_bytes.restype = C.c_size_t
+    lib.sb_workspace_bytes_prefill.argtypes = [P(Config), i32]
+    lib.sb_workspace_bytes_prefill.restype = C.c_size_t
     lib.sb_create.argtypes = [P(Config), P(vp)]
     lib.sb_create.restype = C.c_int
     lib.sb_destroy.argtypes = [vp]

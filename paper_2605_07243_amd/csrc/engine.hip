@@ -45,12 +45,13 @@ struct Dims {
   int R_pre;     // rows of a prefill pass
   int R_cap;     // the larger of the two
   int plan_seqs; // sequences, or pieces of a prefill pass
-  int tpages, dpages, n_chunks, n_chunks_d, n_chunks_f, n_split;
+  int tpages, dpages, n_chunks, n_chunks_d, n_split;
   int adapt_cap;
-  size_t part_elems, o_rows;
+  size_t part_elems, o_rows, logit_elems, rec_elems;
 };
 
-Dims derive(const sb_config& c) {
+// pre_rows: rows that a prefill pass may take (at least cfg.prefill_chunk).
+Dims derive(const sb_config& c, int pre_rows) {
   Dims D{};
   D.S = c.max_seqs;
   D.d = c.target.d_model;
@@ -73,10 +74,11 @@ Dims derive(const sb_config& c) {
   D.bw = ceil_div(D.budget, 32);
   D.vis_words = ceil_div(std::max(D.budget, D.row_cap), 32);
   D.R_dec = std::max(D.S * D.budget, D.S * D.B_max * D.K);
-  // a prefill pass takes kPrefillRows rows, or all that the page tables hold
+  // a prefill pass takes what the workspace allows, or all that the page
+  // tables hold
   D.R_pre = (int)std::min<long>(
-      kPrefillRows, ((long)D.S * c.max_pages * 16 + kPieceRows - 1) / kPieceRows *
-                        kPieceRows);
+      std::min(pre_rows, kPrefillRows),
+      ((long)D.S * c.max_pages * 16 + kPieceRows - 1) / kPieceRows * kPieceRows);
   D.R_cap = std::max(D.R_dec, D.R_pre);
   D.plan_seqs = std::max(D.S, kMaxPieces);
   D.tpages = ceil_div(D.budget, 16);
@@ -88,9 +90,17 @@ Dims derive(const sb_config& c) {
   D.n_chunks = std::max({1, std::min(64, D.V / 2048), min_v});
   D.n_chunks_d = std::max({1, std::min(64, D.Vd / 2048), min_vd});
   D.adapt_cap = c.adapt_cap;
-  // column tiles of the LM heads' fused reduction (at most one per 128
-  // vocabulary ids)
-  D.n_chunks_f = (std::max(D.V, D.Vd) + 127) / 128;
+  // the library's own logits (a drafting block's; bf16 verification reduces
+  // in the LM head's epilogue), and the reductions' records: top-10 of a
+  // drafting block, top-1 of verified rows (bf16: of the epilogue's column
+  // tiles, at most one per 128 vocabulary ids)
+  const size_t draft_rows = (size_t)D.S * D.B_max * D.K;
+  const size_t verify_rows = (size_t)D.S * D.budget;
+  D.logit_elems = std::max(draft_rows * D.Vd,
+                           D.es == 2 ? 0 : verify_rows * D.V);
+  D.rec_elems =
+      std::max(draft_rows * D.n_chunks_d * kVocabRec10,
+               verify_rows * (D.es == 2 ? (D.V + 127) / 128 : D.n_chunks) * 5);
   D.n_split = 32;
   // partial attention rows: up to n_split splits of a drafting or verify
   // row, fewer of a prefill pass (which has rows enough to fill the chip): two,
@@ -98,19 +108,15 @@ Dims derive(const sb_config& c) {
   D.o_rows = std::max((size_t)D.n_split * D.R_dec,
                       (size_t)std::max(2, ceil_div(c.max_pages, 1024)) * D.R_pre);
   // partial-sum buffer: the largest ks * rows * N over the projections and
-  // row capacities (a call's K-chunks are its row capacity * N apart; the
-  // plan changes at multiples of 32 rows, or at one row past or short of one)
+  // row capacities (a call's K-chunks are its row capacity * N apart)
   auto upd = [&](int N, int Kd) {
-    for (int m = 32; m < D.R_cap + 32; m += 32) {
-      int ks = 1;
-      for (const int r : {m - 31, m - 1, m})
-        ks = std::max(ks, gemm_plan(N, Kd, r, D.es, true).ks);
-      D.part_elems = std::max(D.part_elems, (size_t)ks * m * N);
-    }
+    for (int m = 1; m <= D.R_cap; ++m)
+      D.part_elems = std::max(
+          D.part_elems, (size_t)gemm_plan(N, Kd, m, D.es, true).ks * m * N);
   };
   upd(D.qkv_n, D.d);
   upd(D.d, D.H * D.hd);
-  upd(2 * D.F, D.d);
+  if (D.es == 4) upd(2 * D.F, D.d);   // (bf16: SwiGLU in the GEMM's epilogue)
   upd(D.d, D.F);
   upd(D.d, 3 * D.d);
   upd(D.d, 2 * D.d);
@@ -236,7 +242,7 @@ static size_t layout(const Dims& D, void* base, sb_ctx* c) {
   float* o_part = cv.take<float>(D.o_rows * D.H * D.hd * 4);
   float* ml = cv.take<float>(D.o_rows * D.H * 2 * 4);
   int* split_rows = cv.take<int>(R * 4);
-  float* logits = cv.take<float>((size_t)D.R_dec * D.V * 4);
+  float* logits = cv.take<float>(D.logit_elems * 4);
   float* row_lse = cv.take<float>((size_t)D.S * D.row_cap * 4);
   // head-update region (its own buffers: the update may run on another
   // stream while inference uses the ones above)
@@ -254,9 +260,7 @@ static size_t layout(const Dims& D, void* base, sb_ctx* c) {
   int* ad_n = cv.take<int>(4);
   SampleStat* node_stats = cv.take<SampleStat>(
       sample_scratch(D.S, D.budget, sample_blocks(D.V)) * sizeof(SampleStat));
-  float* vpart = cv.take<float>((size_t)D.R_dec *
-                                 std::max(D.n_chunks, D.n_chunks_f) *
-                                 kVocabRec10 * 4);
+  float* vpart = cv.take<float>(D.rec_elems * 4);
   float* cond_buf = cv.take<float>(R * D.d * 4);
   float* taps_pf = cv.take<float>((size_t)(D.R_pre + 1) * 3 * D.d * 4);
   int* taps_idx = cv.take<int>(R * 4);
@@ -468,7 +472,14 @@ int32_t sb_row_capacity(const sb_config* cfg) {
 size_t sb_workspace_bytes(const sb_config* cfg) {
   std::string m;
   if (validate_cfg(cfg, m) != SB_OK) return 0;
-  return layout(derive(*cfg), nullptr, nullptr);
+  return layout(derive(*cfg, cfg->prefill_chunk), nullptr, nullptr);
+}
+
+size_t sb_workspace_bytes_prefill(const sb_config* cfg, int32_t prefill_rows) {
+  std::string m;
+  if (validate_cfg(cfg, m) != SB_OK) return 0;
+  return layout(derive(*cfg, std::max(prefill_rows, cfg->prefill_chunk)),
+                nullptr, nullptr);
 }
 
 int sb_create(const sb_config* cfg, sb_ctx** out) {
@@ -479,7 +490,7 @@ int sb_create(const sb_config* cfg, sb_ctx** out) {
   if (rc != SB_OK) return fail(nullptr, rc, m);
   sb_ctx* c = new sb_ctx();
   c->cfg = *cfg;
-  c->D = derive(*cfg);
+  c->D = derive(*cfg, cfg->prefill_chunk);
   *out = c;
   return SB_OK;
 }
@@ -576,10 +587,16 @@ int sb_bind(sb_ctx* c, const sb_target_weights* tw,
     const int rc = check_layer(c, dw->layers[i], true);
     if (rc) return rc;
   }
-  const size_t need = layout(c->D, nullptr, nullptr);
+  const size_t need = sb_workspace_bytes(&c->cfg);
   if (bad_ptr(ws, kAlign)) return fail(c, SB_EINVAL, "workspace NULL or not 256-byte aligned");
   if (ws_bytes < need)
     return fail(c, SB_EBUDGET, "workspace too small: need " + std::to_string(need));
+  // the longest prefill passes that the workspace holds
+  int pre_rows = kPrefillRows;
+  while (pre_rows > c->cfg.prefill_chunk &&
+         sb_workspace_bytes_prefill(&c->cfg, pre_rows) > ws_bytes)
+    pre_rows -= kPieceRows;
+  c->D = derive(c->cfg, std::max(pre_rows, c->cfg.prefill_chunk));
   c->tw = *tw;
   c->tl.assign(tw->layers, tw->layers + c->D.L);
   c->tw.layers = c->tl.data();
@@ -1035,15 +1052,15 @@ int commit_impl(sb_ctx* c, sb_seqs* sq, const sb_tree* t,
 
 // Prefill: the prompts, one after the other, as one stream of rows that runs
 // through the target, and then through the drafter, in passes of up to R_pre
-// rows.  Prompt rows depend on earlier rows of their own prompt only through
+// rows (2048, or what the workspace allows).  Prompt rows depend on earlier rows of their own prompt only through
 // the K/V cache, which each layer's RoPE launch writes before the layer's
 // attention reads it, so a pass may hold many rows of one prompt and rows of
 // many prompts: the projections then run at MFMA speed instead of streaming
 // every weight again for each 128 rows (8B shape, 4 layers: 1024 rows of one
 // prompt 7.7 -> 3.0 ms, 16 prompts of 512-2048 rows 179 -> 57 ms).  For the
-// attention a pass is cut into pieces of at most kPieceRows rows of one
-// prompt, which start at a multiple of kPieceRows; a pass ends where the next
-// piece does not fit.  The roots come from one LM head after the last pass.
+// attention a pass is cut into pieces of at most kPieceRows rows (R_pre where
+// that is less) of one prompt, which start at a multiple of that; a pass ends
+// where the next piece does not fit.  The roots come from one LM head after the last pass.
 template <typename T>
 int prefill_impl(sb_ctx* c, const sb_seqs* sq, const int32_t* prompt, int ld,
                  const int32_t* lens, sb_kv* tkv, sb_kv* dkv, hipStream_t st) {
@@ -1056,6 +1073,7 @@ int prefill_impl(sb_ctx* c, const sb_seqs* sq, const int32_t* prompt, int ld,
   int longest = 0;
   for (int s = 0; s < sq->n_seqs; ++s) longest = std::max(longest, lens[s]);
   c->T_bound = longest + 1;
+  const int piece = std::min(kPieceRows, D.R_pre);
   int s = 0, a = 0;   // next prompt row
   int n_ended = 0;
   while (s < sq->n_seqs) {
@@ -1065,7 +1083,7 @@ int prefill_impl(sb_ctx* c, const sb_seqs* sq, const int32_t* prompt, int ld,
     int piece_rows = 0;
     tpf.max_keys = 0;
     while (s < sq->n_seqs && pass.n_pieces < kMaxPieces) {
-      const int n = std::min(kPieceRows, lens[s] - a);
+      const int n = std::min(piece, lens[s] - a);
       if (pass.n_rows + n > D.R_pre) break;
       const int j = pass.n_pieces++;
       pass.seq[j] = (unsigned char)s;

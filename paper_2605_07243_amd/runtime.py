@@ -42,11 +42,13 @@ class Runtime:
 
     weights: dict name -> array (the synth naming), host numpy or device
     tensors; ``None`` generates N(0, 0.02) weights on the device.
+    prefill_rows: prompt rows that a prefill pass may take (the workspace is
+    sized for them; prefill_chunk is the least).
     """
 
     def __init__(self, w, weights=None, *, n_seqs=None, max_pages=None,
                  prefill_chunk=128, device="cuda", page_seed=3, seed=0,
-                 adapt_cap=0, share_layers=False):
+                 adapt_cap=0, share_layers=False, prefill_rows=2048):
         self.lib = B.load()
         self.w = w
         self.dev = torch.device(device)
@@ -83,7 +85,7 @@ class Runtime:
         # device weights (full-depth tests whose oracle shares one layer)
         self.share_layers = share_layers
         self._weights(weights, seed)
-        nbytes = self.lib.sb_workspace_bytes(C.byref(cfg))
+        nbytes = self.lib.sb_workspace_bytes_prefill(C.byref(cfg), prefill_rows)
         self.workspace = torch.empty(nbytes, dtype=torch.uint8,
                                      device=self.dev)
         B.check(self.lib, ctx, self.lib.sb_bind(

@@ -52,3 +52,35 @@ def test_prefill_passes(dtype, lens):
                     e = rel_err(x[layer].reshape(st.T, -1),
                                 np.asarray(ref[layer]).reshape(st.T, -1))
                     assert e.max() < tol, (which, s, layer, e.argmax())
+
+
+@pytest.mark.parametrize("dtype,chunk,lens", [
+    ("f32", 16, [63, 1, 40]),
+    ("f32", 48, [97, 17]),
+    ("bf16", 16, [33, 65, 1]),
+    ("bf16", 96, [200, 31]),
+    ("bf16", 512, [513]),
+])
+def test_prefill_passes_in_the_least_workspace(dtype, chunk, lens):
+    """Passes of prefill_chunk rows: pieces of fewer rows than 64, passes that
+    end inside a prompt and that one piece fills."""
+    w = _workload(dtype, len(lens))
+    tol = 1e-4 if dtype == "f32" else 2e-2
+    weights, tgt, dr = models(w)
+    prompts = synth.prompts(w, lengths=lens)
+    rt = runtime(w, weights, max_pages=(max(lens) + 16) // 16,
+                 prefill_chunk=chunk, prefill_rows=0)
+    print("[passes] least workspace", dtype, chunk, lens, flush=True)
+    rt.prefill(prompts)
+    torch.cuda.synchronize()
+    for s, pr in enumerate(prompts):
+        st = specdec.prefill(tgt, dr, pr)
+        assert int(rt.T[s]) == st.T
+        assert rel_err(host(rt.cond_taps[s]), st.cond_taps).max() < tol
+        for which, kv in (("target", st.tkv), ("drafter", st.dkv)):
+            got = rt.read_cache(which, s, st.T)
+            for layer in range(len(kv.k)):
+                for x, ref in ((got[0], kv.k), (got[1], kv.v)):
+                    e = rel_err(x[layer].reshape(st.T, -1),
+                                np.asarray(ref[layer]).reshape(st.T, -1))
+                    assert e.max() < tol, (which, s, layer, e.argmax())
