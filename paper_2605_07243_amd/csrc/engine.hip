@@ -943,7 +943,7 @@ int lm_head_reduce(sb_ctx* c, const void* A, const void* W, int V,
                  out_row);
     return launch_gemm_vocab(static_cast<const bf16_t*>(A), D.d,
                              static_cast<const bf16_t*>(W), V, D.d,
-                             logits_out, n, cap, topk, c->vpart, st);
+                             logits_out, n, cap, c->vpart, st);
   } else {
     float* logits = logits_out ? logits_out : c->logits;
     lm_head<T>(c, A, W, V, logits, n, cap, st);

@@ -63,26 +63,14 @@ __device__ __forceinline__ f32x16_t mma_32x32x16(u32x4_t a, u32x4_t b,
 __device__ __forceinline__ float silu(float x) { return x / (1.0f + expf(-x)); }
 
 // Vocabulary records of the LM-head epilogue (the same record the separate
-// reduction writes: KT values, KT ids as int bits, then m, s = sum exp(z - m)
-// and u = sum exp(z - m) z).  Top-KT keeps the larger value first, equal
-// values ordered by the smaller id.
-template <int KT>
-__device__ __forceinline__ void vr_insert(float (&tv)[KT], int (&ti)[KT],
-                                          float v, int id) {
-  if (!better(v, id, tv[KT - 1], ti[KT - 1])) return;
-  tv[KT - 1] = v;
-  ti[KT - 1] = id;
-#pragma unroll
-  for (int j = KT - 1; j > 0; --j) {
-    if (better(tv[j], ti[j], tv[j - 1], ti[j - 1])) {
-      const float a = tv[j];
-      tv[j] = tv[j - 1];
-      tv[j - 1] = a;
-      const int b = ti[j];
-      ti[j] = ti[j - 1];
-      ti[j - 1] = b;
-    }
-  }
+// top-1 reduction writes): the largest value, its id as int bits (the smaller
+// of equal values' ids), then m, s = sum exp(z - m) and u = sum exp(z - m) z.
+constexpr int kVocabRec = 5;
+
+__device__ __forceinline__ void vr_best(float& v, int& id, float v2, int id2) {
+  if (!better(v2, id2, v, id)) return;
+  v = v2;
+  id = id2;
 }
 
 __device__ __forceinline__ void vr_stats_merge(float& m, float& s, float& u,
@@ -97,15 +85,15 @@ __device__ __forceinline__ void vr_stats_merge(float& m, float& s, float& u,
 
 // MF: 32-row activation tiles per workgroup; NF: 32-row weight fragments
 // per wave; PF: K-stages (64 columns each) of weights in flight per wave.
-// VR > 0 (LM heads, one K-chunk): besides (or, with P == nullptr, instead
+// VOCAB (LM heads, one K-chunk): besides (or, with P == nullptr, instead
 // of) the fp32 outputs, each workgroup writes for every row the vocabulary
-// record (top VR, m, s, u) of its 128 NF output columns to
-// rec[(row * n_nt + column tile) * (2 VR + 3)].  n_first (a multiple of
-// 32 NF; 0 with VR > 0): the launch covers weight rows n_first .. N - 1, in
+// record of its 128 NF output columns to
+// rec[(row * n_nt + column tile) * kVocabRec].  n_first (a multiple of
+// 32 NF; 0 with VOCAB): the launch covers weight rows n_first .. N - 1, in
 // n_nt column tiles from there.  What the first loads need stands first
 // among the arguments: the first 14 dwords arrive in registers with the
 // wave (kernel argument preload), the others cost a scalar load each.
-template <int MF, int NF, int PF, bool SWIGLU, int VR>
+template <int MF, int NF, int PF, bool SWIGLU, bool VOCAB>
 __global__ __launch_bounds__(256) void gemm_tile_kernel(
     const bf16_t* X, const bf16_t* W, const int* __restrict__ m_count, int ldx,
     int K, int N, int k_chunk, int n_mt, int n_nt, int n_first, int x_rows,
@@ -270,19 +258,13 @@ __global__ __launch_bounds__(256) void gemm_tile_kernel(
 #undef SB_ISSUE_W
 #undef SB_ISSUE_WI
 #undef SB_SCHED
-  if constexpr (VR > 0) {
-    constexpr int RL = 2 * VR + 3;
-    __shared__ float vrec[4][32 * MF][RL];
+  if constexpr (VOCAB) {
+    __shared__ float vrec[4][32 * MF][kVocabRec];
 #pragma unroll
     for (int t = 0; t < MF; ++t) {
       const int m = m_base + 32 * t + lr;
-      float tv[VR];
-      int ti[VR];
-#pragma unroll
-      for (int k = 0; k < VR; ++k) {
-        tv[k] = -FLT_MAX;
-        ti[k] = 0x7FFFFFFF;
-      }
+      float tv = -FLT_MAX;
+      int ti = 0x7FFFFFFF;
       float mx = -FLT_MAX, sm = 0.f, su = 0.f;
       if (wave_on) {
         // the logits go out first: their stores drain under the statistics
@@ -298,7 +280,6 @@ __global__ __launch_bounds__(256) void gemm_tile_kernel(
         // lane register r of fragment f is column nb + 32 f + 8 (r / 4) +
         // 4 h + r % 4 of row m, ascending in (f, r): the first maximum is the
         // last one found from behind
-        static_assert(VR == 1, "top-1 records");
 #pragma unroll
         for (int f = 0; f < NF; ++f)
 #pragma unroll
@@ -309,8 +290,8 @@ __global__ __launch_bounds__(256) void gemm_tile_kernel(
 #pragma unroll
           for (int r = 15; r >= 0; --r)
             at = acc[t][f][r] == mx ? 32 * f + 8 * (r >> 2) + (r & 3) : at;
-        tv[0] = mx;
-        if (at >= 0) ti[0] = nb + 4 * h + at;
+        tv = mx;
+        if (at >= 0) ti = nb + 4 * h + at;
 #pragma unroll
         for (int f = 0; f < NF; ++f)
 #pragma unroll
@@ -322,60 +303,42 @@ __global__ __launch_bounds__(256) void gemm_tile_kernel(
       }
       // the lane pair (h = 0, 1) holds the same row
       {
-        float pv[VR];
-        int pi[VR];
-#pragma unroll
-        for (int k = 0; k < VR; ++k) {
-          pv[k] = __shfl_xor(tv[k], 32, 64);
-          pi[k] = __shfl_xor(ti[k], 32, 64);
-        }
+        const float pv = __shfl_xor(tv, 32, 64);
+        const int pi = __shfl_xor(ti, 32, 64);
         const float m2 = __shfl_xor(mx, 32, 64);
         const float s2 = __shfl_xor(sm, 32, 64);
         const float u2 = __shfl_xor(su, 32, 64);
-#pragma unroll
-        for (int k = 0; k < VR; ++k) vr_insert<VR>(tv, ti, pv[k], pi[k]);
+        vr_best(tv, ti, pv, pi);
         vr_stats_merge(mx, sm, su, m2, s2, u2);
       }
       if (h == 0) {
         float* o = vrec[wave][32 * t + lr];
-#pragma unroll
-        for (int k = 0; k < VR; ++k) {
-          o[k] = tv[k];
-          o[VR + k] = __int_as_float(ti[k]);
-        }
-        o[2 * VR] = mx;
-        o[2 * VR + 1] = sm;
-        o[2 * VR + 2] = su;
+        o[0] = tv;
+        o[1] = __int_as_float(ti);
+        o[2] = mx;
+        o[3] = sm;
+        o[4] = su;
       }
     }
     __syncthreads();
     // one thread per row merges the four waves' records
     if (tid < 32 * MF && m_base + tid < M) {
-      float tv[VR];
-      int ti[VR];
       const float* o0 = vrec[0][tid];
-#pragma unroll
-      for (int k = 0; k < VR; ++k) {
-        tv[k] = o0[k];
-        ti[k] = __float_as_int(o0[VR + k]);
-      }
-      float mx = o0[2 * VR], sm = o0[2 * VR + 1], su = o0[2 * VR + 2];
+      float tv = o0[0];
+      int ti = __float_as_int(o0[1]);
+      float mx = o0[2], sm = o0[3], su = o0[4];
 #pragma unroll
       for (int w = 1; w < 4; ++w) {
         const float* ow = vrec[w][tid];
-#pragma unroll
-        for (int k = 0; k < VR; ++k) vr_insert<VR>(tv, ti, ow[k], __float_as_int(ow[VR + k]));
-        vr_stats_merge(mx, sm, su, ow[2 * VR], ow[2 * VR + 1], ow[2 * VR + 2]);
+        vr_best(tv, ti, ow[0], __float_as_int(ow[1]));
+        vr_stats_merge(mx, sm, su, ow[2], ow[3], ow[4]);
       }
-      float* g = rec + ((size_t)(m_base + tid) * n_nt + nt) * RL;
-#pragma unroll
-      for (int k = 0; k < VR; ++k) {
-        g[k] = tv[k];
-        g[VR + k] = __int_as_float(ti[k]);
-      }
-      g[2 * VR] = mx;
-      g[2 * VR + 1] = sm;
-      g[2 * VR + 2] = su;
+      float* g = rec + ((size_t)(m_base + tid) * n_nt + nt) * kVocabRec;
+      g[0] = tv;
+      g[1] = __int_as_float(ti);
+      g[2] = mx;
+      g[3] = sm;
+      g[4] = su;
     }
     return;
   }
@@ -619,8 +582,7 @@ GemmPlan gemm_plan(int N, int K, int m_cap, int elem_bytes, bool retile) {
     // weight tiles, 2 K-chunks); 384 rows x 8192 x 8192 58 -> 54 us and
     // x 28672 188 -> 178 us (96-row tiles); 96-row tiles at 192 rows made
     // the 70B drafting block 7% slower, so they need 256 rows or more.  The
-    // K-split stays within the one-row plan's (the partial buffers are
-    // sized for it).
+    // K-split stays within the one-row plan's, as where these were measured.
     const int ks_cap = pick_split((N + 127) / 128, K, 2);
     const double base = many_row_us(g.mf, g.nf, g.ks, N, K, m_cap);
     double best = 0.92 * base;
@@ -664,7 +626,7 @@ bool gemm_time_pending() { return g_ev_start != nullptr; }
 
 namespace {
 
-template <bool SWIGLU, int VR = 0>
+template <bool SWIGLU, bool VOCAB = false>
 void launch_tile(const GemmPlan& g, const bf16_t* X, int ldx, const bf16_t* W,
                  int N, int K, float* P, size_t part_stride,
                  const int* m_count, int m_cap, int ks, bf16_t* act, int F,
@@ -681,9 +643,9 @@ void launch_tile(const GemmPlan& g, const bf16_t* X, int ldx, const bf16_t* W,
   if (g.mf == MF_ && g.nf == NF_ && g.pf == PF_) {                            \
     hipEvent_t ea, eb;                                                        \
     take_events(ea, eb);                                                      \
-    hipExtLaunchKernelGGL(gemm_tile_kernel<MF_, NF_, PF_, SWIGLU, VR>, grid,  \
-                          dim3(256), 0, st, ea, eb, 0, X, W, m_count, ldx, K, \
-                          N, k_chunk, n_mt, n_nt, n_first,                    \
+    hipExtLaunchKernelGGL(gemm_tile_kernel<MF_, NF_, PF_, SWIGLU, VOCAB>,     \
+                          grid, dim3(256), 0, st, ea, eb, 0, X, W, m_count,   \
+                          ldx, K, N, k_chunk, n_mt, n_nt, n_first,            \
                           rows_likely_empty() ? 0 : m_cap, P, part_stride,    \
                           act, F, rec);                                       \
     return;                                                                   \
@@ -694,8 +656,8 @@ void launch_tile(const GemmPlan& g, const bf16_t* X, int ldx, const bf16_t* W,
   SB_LAUNCH(4, 1, 4)
   SB_LAUNCH(4, 2, 2)
   SB_LAUNCH(4, 4, 2)
-  if constexpr (VR == 0) SB_LAUNCH(4, 3, 2)   // re-tiled or split launches
-  if constexpr (VR == 0) SB_LAUNCH(3, 2, 2)
+  if constexpr (!VOCAB) SB_LAUNCH(4, 3, 2)   // re-tiled or split launches
+  if constexpr (!VOCAB) SB_LAUNCH(3, 2, 2)
 #undef SB_LAUNCH
 }
 
@@ -749,10 +711,9 @@ template int launch_gemm_xwt<bf16_t>(const bf16_t*, int, const bf16_t*, int,
 
 int launch_gemm_vocab(const bf16_t* X, int ldx, const bf16_t* W, int N,
                       int K, float* logits, const int* m_count, int m_cap,
-                      int topk, float* rec, hipStream_t st) {
+                      float* rec, hipStream_t st) {
   const GemmPlan g = gemm_plan(N, K, m_cap, 2);
-  if (topk != 1) return 0;
-  launch_tile<false, 1>(g, X, ldx, W, N, K, logits, 0, m_count, m_cap, 1,
+  launch_tile<false, true>(g, X, ldx, W, N, K, logits, 0, m_count, m_cap, 1,
                         nullptr, 0, st, rec);
   return gemm_vocab_chunks(N, K, m_cap);
 }
