@@ -368,8 +368,8 @@ def _fake_tree():
 
 
 def test_noalloc_accept_rejects_sizes_past_its_static_scratch(lib):
-    """sb_accept_sample_noalloc keeps n_seqs * budget * ceil(vocab / 16384)
-    tile statistics in a static array of 65536 entries: 8 x 512 x 16 fits
+    """sb_accept_sample_noalloc keeps the statistics of n_seqs * budget *
+    ceil(vocab / 16384) tiles in a static array for 65536: 8 x 512 x 16 fits
     exactly, 9 sequences do not (SB_EBUDGET, before any device work); the
     signal r needs a bound context (SB_ESTATE)."""
     c = cfg(t_vocab=262144, budget=512, max_seqs=16)

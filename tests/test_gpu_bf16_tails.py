@@ -40,13 +40,14 @@ def test_iteration_calls_width_tails():
 
 
 def test_prefill_chunks_width_tails():
-    """Device prefill in 64-row chunks against the oracle's prefill."""
+    """Device prefill in 64-row chunks (the passes of the least workspace)
+    against the oracle's prefill."""
     import numpy as np
     import torch
     from gpu_harness import host, rel_err
     weights, tgt, dr = models(W)
     prompts = synth.prompts(W)
-    rt = runtime(W, weights, max_pages=24, prefill_chunk=64)
+    rt = runtime(W, weights, max_pages=24, prefill_chunk=64, prefill_rows=0)
     rt.prefill(prompts)
     torch.cuda.synchronize()
     for s, pr in enumerate(prompts):

@@ -3,8 +3,8 @@ static scratch) against the workspace entry point sb_accept_sample, through
 the C ABI: identical paths, accepted counts, bonus tokens and signals on the
 same trees, logits and uniforms, for two calls in a row (the second with
 fewer sequences and smaller trees, so the scratch holds the first call's
-larger contents), in both call orders.  The vocabulary spans eight 16384-token
-statistics tiles."""
+larger contents), in both call orders.  The vocabulary spans eight of the
+16384-token tiles that the scratch is counted in."""
 import numpy as np
 import pytest
 import torch
