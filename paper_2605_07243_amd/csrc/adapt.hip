@@ -279,7 +279,9 @@ void launch_lm_update(T* W, int Vd, int d, const float* G, const T* A, T* At,
   if constexpr (sizeof(T) == 2) {
     lm_operand_kernel<<<d / 64, 256, 0, st>>>(A, d, n_eff, At);
     // two workgroups fit a CU: halves of the columns, for rounds of 512 even
-    // enough with a full vocabulary's 1002 groups of row blocks
+    // enough with a full vocabulary's 1002 groups of row blocks (2004
+    // workgroups).  A reduced vocabulary fills less of the chip: 500
+    // workgroups at 32000 tokens, 126 at 8000; finer splits are not measured
     const int kb_per = (d / 64 + 1) / 2;
     lm_update_kernel<<<dim3((Vd / 32 + 3) / 4, 2), 256, 0, st>>>(
         W, Vd, d, G, At, n_eff, lr, kb_per);
@@ -298,6 +300,8 @@ void launch_rank_update(float* rank_w, float* rank_b, const float* ds,
       rank_w, rank_b, ds, h, psi, d, n_eff, lr, loss, loss_out, count);
 }
 
+// Granularity of d_model that a head update accepts.  For fp32 the columns of
+// a workgroup; the bf16 kernels work in 64 columns, the interface's 256 stands.
 int adapt_column_width(int elem_bytes) { return elem_bytes == 2 ? 256 : 128; }
 int adapt_stripe_rows() { return kStripeRows; }
 

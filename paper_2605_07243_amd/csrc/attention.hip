@@ -3,7 +3,9 @@
 // Every query row of a sequence attends to all committed prefix entries
 // and to the segment slots whose bit is set in its visibility words (tree
 // ancestors-or-self for verification, on-path rows of earlier blocks plus
-// its own block's rows <= k for the drafter, a causal chain for prefill).
+// its own block's rows <= k for the drafter).  Prefill rows have no segment:
+// their keys are in the paged cache already, and a row attends to the entries
+// up to its own.
 //
 // A q-tile is 16 query vectors of one KV head (grouped-query attention: the
 // G = H / Hkv query heads of a row share the KV head, so the 16 vectors are
@@ -194,6 +196,10 @@ __global__ __launch_bounds__(NQ * KS * 64) void tree_attn_kernel(
   // values are used raw until the stash / compute of the tile (an empty
   // half reads page 0: its keys are masked and its V slots zeroed there),
   // so no load is consumed before its turn and the ring stays in flight.
+  // With key groups (KS > 1) that holds only in part: the compiler keeps the
+  // K half of slot 0 in scratch memory (48 to 144 bytes a lane; none with
+  // KS = 1), so those loads are waited for and stored before the tile in
+  // hand is computed.
   // (two: with four the unrolled loop was 17 KB of code, fetched anew by
   // every launch; 8 layers over 1024 keys 1193 -> 1179 us)
   constexpr int DEPTH = 2;
@@ -1162,10 +1168,11 @@ int attn_qgroups(int rows_per_seq_cap, int G, int seq_heads, int es) {
 int attn_workgroup_target(int rows_per_seq_cap, int G, int seq_heads, int es) {
   if (!attn_shape(rows_per_seq_cap, G, seq_heads, es).mfma32)
     return 2 * kAttnSlots;
-  // at most 32 query vectors per KV head (catch-up rows, first blocks of many
-  // sequences): partials are small, and two workgroups of four waves fit a
-  // CU, so the prefix is cut for 512 (16 sequences x 1 row over 512-2048 keys:
-  // 41 us for 256 workgroups, 38 for 512, 55 for 1024)
+  // at most 32 query vectors per KV head (catch-up rows; drafting blocks whose
+  // B_max K rows per sequence, the bound that a first block is launched with
+  // too, are that few): partials are small, and two workgroups of four waves
+  // fit a CU, so the prefix is cut for 512 (16 sequences x 1 row over 512-2048
+  // keys: 41 us for 256 workgroups, 38 for 512, 55 for 1024)
   return rows_per_seq_cap * G <= 32 ? 2 * kAttnSlots : kAttnSlots;
 }
 

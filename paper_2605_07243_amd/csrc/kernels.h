@@ -168,10 +168,11 @@ int attn_qgroups(int rows_per_seq_cap, int G, int seq_heads, int es);
 int attn_workgroup_target(int rows_per_seq_cap, int G, int seq_heads, int es);
 
 // Vocabulary reductions over fp32 logits [cap][V], in chunks of at most
-// kVocabChunkMax logits (a chunk is staged in LDS); a row needs at least
-// ceil(V / kVocabChunkMax) record slots.
+// kVocabChunkMax logits (a workgroup holds a chunk in registers, at most
+// twelve float4 a thread).
 constexpr int kVocabChunkMax = 12288;
-// Returns the number of chunk records written per row (<= max_chunks).
+// Returns the number of chunk records written per row: at most the larger of
+// max_chunks and ceil(V / kVocabChunkMax).
 int launch_vocab_partial(const float* logits, const int* n, int cap, int V,
                          int max_chunks, int topk, float* part,
                          hipStream_t st);

@@ -297,6 +297,12 @@ int launch_vocab_partial(const float* logits, const int* n, int cap, int V,
   n_chunks = std::max(n_chunks, (V + kVocabChunkMax - 1) / kVocabChunkMax);
   const int chunk = (((V + n_chunks - 1) / n_chunks) + 3) & ~3;
   const dim3 grid(n_chunks, cap);
+  // Twelve float4 a thread hold any chunk, with the rest of a short one
+  // skipped.  Three hold the chunks of up to 3072 logits that launches of few
+  // rows make: a toy model's verification (1024 logits) 98.3 -> 97.9 us, no
+  // difference at 128256 in chunks of 2004 (first block 377.8 us with both).
+  // A form between the two, for a head update's chunks of 4008, is not
+  // measured.
 #define SB_VOCAB(NV_)                                                         \
   if (chunk <= 1024 * NV_) {                                                  \
     auto k = topk == 1 ? vocab_partial_kernel<1, NV_>                         \
