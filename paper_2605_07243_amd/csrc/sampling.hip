@@ -6,7 +6,9 @@
 // when u_acc[c] < r(x), else x leaves the residual.  A child whose token was
 // already rejected has residual probability zero and is skipped.  When no
 // child is taken, the bonus token is drawn from the residual by inverse
-// transform over increasing token ids with u_bonus[n].  Every emitted token
+// transform over increasing token ids with u_bonus[n].  A row with a logit
+// that is NaN or +inf has no distribution: no child is taken there, and the
+// bonus is token 0.  Every emitted token
 // is then distributed as the target's (speculative sampling applied
 // recursively over a node's candidates).
 //
@@ -54,8 +56,8 @@ __device__ __forceinline__ int row_offset(const int* __restrict__ n_nodes,
   return wave_sum_i(lane < s ? min(n_nodes[lane], budget) : 0);
 }
 
-// A wave's 1024 tokens of a block, four float4 a lane; -FLT_MAX (exp = 0)
-// past the vocabulary.  QS: token stride between a lane's float4 (256: one
+// A wave's 1024 tokens of a block, four float4 a lane; -inf (exp = 0) past
+// the vocabulary.  QS: token stride between a lane's float4 (256: one
 // contiguous KiB per load; 4: sixteen consecutive tokens per lane).
 template <int QS>
 __device__ __forceinline__ void load_block(const float* __restrict__ z, int V,
@@ -64,7 +66,7 @@ __device__ __forceinline__ void load_block(const float* __restrict__ z, int V,
   for (int q = 0; q < 4; ++q) {
     const int e = kSampleBlock * b + QS * q + (QS == 256 ? 4 : 16) * lane;
     v[q] = e < V ? *reinterpret_cast<const float4*>(z + e)
-                 : make_float4(-FLT_MAX, -FLT_MAX, -FLT_MAX, -FLT_MAX);
+                 : make_float4(-INFINITY, -INFINITY, -INFINITY, -INFINITY);
   }
 }
 
@@ -127,14 +129,14 @@ __global__ __launch_bounds__(kThreads) void node_stats_kernel(
   for (int k = 0; k < 4; ++k) {
     const int b = b0 + 4 * k;
     if (b >= n_blk) break;
-    float m = -FLT_MAX;
+    float m = -INFINITY;
 #pragma unroll
     for (int q = 0; q < 4; ++q)
       m = fmaxf(m, fmaxf(fmaxf(v[k][q].x, v[k][q].y), fmaxf(v[k][q].z, v[k][q].w)));
     m = wave_max(m);
     const float ref = m * inv_t;
     double sum = 0.0;
-    if (m > -FLT_MAX) {
+    if (ref > -INFINITY) {      // (a logit of the type's lowest value counts)
 #pragma unroll
       for (int q = 0; q < 4; ++q)
         sum += ((double)__expf(v[k][q].x * inv_t - ref) +
@@ -171,7 +173,7 @@ __device__ __forceinline__ float merge_stats(const float (&bm)[kLaneBlocks],
   float sum = 0.f;
 #pragma unroll
   for (int k = 0; k < kLaneBlocks; ++k)
-    if (bs[k] > 0.0) sum += (float)bs[k] * __expf(bm[k] - m);
+    if (bs[k] != 0.0) sum += (float)bs[k] * __expf(bm[k] - m);   // NaN stays
   return m + logf(wave_sum(sum));
 }
 
@@ -215,7 +217,7 @@ __device__ __forceinline__ void sample_walk(
     }
     nk = min(nk, kMaxKids);
     wave_lds_sync();
-    float zk = -FLT_MAX;
+    float zk = -INFINITY;
     if (lane < nk) {
       const int x = tr.tok[kid[lane]];
       // a token outside the vocabulary has no target mass
@@ -227,7 +229,7 @@ __device__ __forceinline__ void sample_walk(
       break;
     }
     const float l = merge_stats(bm, bs);
-    if (lane < nk) kp[lane] = zk > -FLT_MAX ? __expf(zk * inv_t - l) : 0.f;
+    if (lane < nk) kp[lane] = zk > -INFINITY ? __expf(zk * inv_t - l) : 0.f;
     wave_lds_sync();
     // sequential tests (lane 0), result broadcast through LDS
     if (lane == 0) {
@@ -282,7 +284,7 @@ __device__ __forceinline__ int sample_draw(
   // without the rejected ones
 #pragma unroll
   for (int k = 0; k < kLaneBlocks; ++k)
-    bs[k] = bs[k] > 0.0 ? bs[k] * (double)__expf(bm[k] - l) : 0.0;
+    bs[k] = bs[k] != 0.0 ? bs[k] * (double)__expf(bm[k] - l) : 0.0;
 #pragma unroll 1
   for (int r = 0; r < nrej; ++r) {
     const int b = rej[r] / kSampleBlock;
